@@ -252,10 +252,12 @@ int lbfd_set_graphs(lbfd_handle *h, int32_t enable);
 typedef struct {
     int32_t rows;           /* workgroups of the step's node kernels: 64 x rows nodes, rows = 1, 2 or 4
                                (default 4) */
-    int32_t sor_wg_per_cu;  /* persistent grid of the SOR half-sweeps: workgroups of 256 per compute unit,
+    int32_t sor_wg_per_cu;  /* grid of the SOR half-sweep launches: workgroups of 256 per compute unit,
                                1..32 (default 8), capped at one per 256 nodes of a colour */
-    int32_t sor_narrow;     /* workgroups of the sweeps past the third (they usually only find the systems
-                               converged): 8..65536, a multiple of 8 (default 256) */
+    int32_t sor_narrow;     /* most workgroups of the one launch that runs the sweeps past the third (they
+                               usually only find the systems converged): 8..65536, a multiple of 8
+                               (default 256); grids of up to 512 nodes of a colour per compute unit run
+                               every sweep in that launch and do not use it */
 } lbfd_tuning;
 
 /* Set or read a handle's launch shape (lbfd_set_tuning synchronises the stream
@@ -300,10 +302,9 @@ lbfd_handle *lbfd_batch_instance(lbfd_batch *b, int32_t i);
  * (initialised, or set to the same step, together), else EINVAL. Asynchronous. */
 int lbfd_batch_step(lbfd_batch *b, int64_t n);
 
-/* Launch shape of every instance of a batch: `rows` for the node kernels and
- * `sor_narrow` for the SOR sweeps past the third, which run over the instances
- * still converging (the first three sweeps launch one workgroup per SOR tile of
- * every instance, so `sor_wg_per_cu` does not change the batch's launches).
+/* Launch shape of every instance of a batch: `rows` for the node kernels (the
+ * solve's launches follow from the instances alone: `sor_wg_per_cu` and
+ * `sor_narrow` do not change them).
  * Errors: EINVAL, EHIP. */
 int lbfd_batch_set_tuning(lbfd_batch *b, const lbfd_tuning *t);
 

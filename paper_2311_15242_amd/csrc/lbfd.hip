@@ -1065,24 +1065,21 @@ __device__ __forceinline__ void sor_conv(const KP<typename P::R> &k, int color, 
     // sweep s-1: a black half-sweep is skipped once the red half before it found the
     // system converged, and the red half of the next sweep too. Otherwise the
     // pre-update residuals of every row of the previous sweep are tested.
+    const int lane = threadIdx.x & 63;
+    const auto slot = [&](int fi, int e) { return bits_to_double(*res_slot(k.fld.sorres, fi, e, lane)); };
+    // exact: red of sweep s >= 2 tests sweep s-1, black of sweep s >= 1 sweep s
+    const int sw = k.sor_exact ? (color == 0 ? sweep - 1 : sweep) : sweep;
     conv[0] = conv[1] = false;
-    {
-        const int lane = threadIdx.x & 63;
+    if (sw < 1) return;
+    const int e0 = k.sor_exact ? 2 * sw : 2 * (sw - 1), e1 = k.sor_exact ? e0 : e0 + 1;
+    double r[2], b[2];
 #pragma unroll
-        for (int fi = 0; fi < 2; ++fi) {
-            const double b = wave_max(bits_to_double(*res_slot(k.fld.sorres, fi, RMAX_IDX, lane)));
-            double r = -1.0;
-            if (k.sor_exact) {
-                // red of sweep s >= 2: test of sweep s-1; black of sweep s >= 1: test of sweep s
-                const int sw = color == 0 ? sweep - 1 : sweep;
-                if (sw >= 1) r = wave_max(bits_to_double(*res_slot(k.fld.sorres, fi, 2 * sw, lane)));
-            } else if (sweep > 0) {
-                r = fmax(wave_max(bits_to_double(*res_slot(k.fld.sorres, fi, 2 * (sweep - 1), lane))),
-                         wave_max(bits_to_double(*res_slot(k.fld.sorres, fi, 2 * (sweep - 1) + 1, lane))));
-            }
-            conv[fi] = r >= 0.0 && r <= (double)k.tol * b;
-        }
+    for (int fi = 0; fi < 2; ++fi) {
+        b[fi] = slot(fi, RMAX_IDX);
+        r[fi] = fmax(slot(fi, e0), slot(fi, e1));
     }
+#pragma unroll
+    for (int fi = 0; fi < 2; ++fi) conv[fi] = __ballot(!(r[fi] <= (double)k.tol * wave_max(b[fi]))) == 0ull;
 }
 
 // Node (x, y, z) lies on the last plane of an axis that is periodic with an odd
@@ -1112,42 +1109,58 @@ template <class R> __device__ __forceinline__ SorOps<R> sor_ops(const KP<R> &k, 
     return a;
 }
 
-// One SOR update of node (x, y, z) in both implicit systems (a converged system is
-// left alone), recording its pre-update residual and |rhs|. Face neighbours in the
-// interior lie in the other colour plane at the same row offset; across a periodic
-// wrap the neighbour's own parity decides its plane (an odd extent keeps it).
-template <int LAT, class P>
-__device__ __forceinline__ void sor_node(const KP<typename P::R> &k, const SorOps<typename P::R> &a, int x, int y,
-                                         int z, const bool *conv, typename P::R *rloc, typename P::R *bloc)
+// Places of a row of the implicit systems and of its face neighbours in the colour-split
+// arrays. L: the node's index within its colour plane, (x >> 1) + hx (y + ny z). An inside
+// face neighbour lies in the other plane at L plus a constant; across a periodic wrap an
+// even extent keeps that, an odd one (a seam axis) leads back into the own plane. on: the
+// face exists (no wall).
+template <int LAT> struct SorIdx {
+    static constexpr int NF = 2 * Lat<LAT>::D;
+    uint32_t n, q[NF];
+    bool on[NF];
+};
+template <int LAT, class R>
+__device__ __forceinline__ SorIdx<LAT> sor_idx(const KP<R> &k, uint32_t L, int x, int y, int z, int color)
+{
+    SorIdx<LAT> r;
+    const uint32_t own = color ? k.hn : 0u, oth = k.hn - own, hx = k.hx, b = (uint32_t)(x & 1);
+    const auto wrap = [&](int axis) { return ((k.seam >> axis) & 1) ? own : oth; };
+    const uint32_t wx = (uint32_t)((k.nx - 1) >> 1), wy = hx * (uint32_t)(k.ny - 1);
+    r.n = own + L;
+    r.on[0] = x > 0 || !k.bc[0];
+    r.q[0] = x > 0 ? oth + L - 1u + b : wrap(0) + L + wx;
+    r.on[1] = x < k.nx - 1 || !k.bc[0];
+    r.q[1] = x < k.nx - 1 ? oth + L + b : wrap(0) + L - wx;
+    r.on[2] = y > 0 || !k.bc[1];
+    r.q[2] = y > 0 ? oth + L - hx : wrap(1) + L + wy;
+    r.on[3] = y < k.ny - 1 || !k.bc[1];
+    r.q[3] = y < k.ny - 1 ? oth + L + hx : wrap(1) + L - wy;
+    if constexpr (Lat<LAT>::D == 3) {
+        const uint32_t sz = hx * (uint32_t)k.ny, wz = sz * (uint32_t)(k.nz - 1);
+        r.on[4] = z > 0 || !k.bc[2];
+        r.q[4] = z > 0 ? oth + L - sz : wrap(2) + L + wz;
+        r.on[5] = z < k.nz - 1 || !k.bc[2];
+        r.q[5] = z < k.nz - 1 ? oth + L + sz : wrap(2) + L - wz;
+    }
+    return r;
+}
+
+// One SOR update of row r in both implicit systems (a converged system is left alone),
+// recording its pre-update residual and |rhs|.
+// DEV: the iterates are shared with workgroups of the same launch (device-scope accesses).
+template <int LAT, class P, bool DEV = false>
+__device__ __forceinline__ void sor_node(const SorOps<typename P::R> &a, const SorIdx<LAT> &r, const bool *conv,
+                                         typename P::R *rloc, typename P::R *bloc)
 {
     using R = typename P::R;
-    constexpr int D = Lat<LAT>::D, NF = 2 * D;
-    const int nx = k.nx, ny = k.ny, nz = k.nz;
-    const uint32_t n = split_idx(k, x, y, z);
-    const uint32_t hx = k.hx, sz = k.hx * (uint32_t)ny;
-    // the same x >> 1 in the other colour plane
-    const uint32_t o = ((x + y + z) & 1) ? n - k.hn : n + k.hn;
-    uint32_t q[6];
-    bool on[6];
-    on[0] = x > 0 || !k.bc[0];
-    q[0] = x > 0 ? o - (uint32_t)(x >> 1) + (uint32_t)((x - 1) >> 1) : split_idx(k, nx - 1, y, z);
-    on[1] = x < nx - 1 || !k.bc[0];
-    q[1] = x < nx - 1 ? o - (uint32_t)(x >> 1) + (uint32_t)((x + 1) >> 1) : split_idx(k, 0, y, z);
-    on[2] = y > 0 || !k.bc[1];
-    q[2] = y > 0 ? o - hx : split_idx(k, x, ny - 1, z);
-    on[3] = y < ny - 1 || !k.bc[1];
-    q[3] = y < ny - 1 ? o + hx : split_idx(k, x, 0, z);
-    if constexpr (D == 3) {
-        on[4] = z > 0 || !k.bc[2];
-        q[4] = z > 0 ? o - sz : split_idx(k, x, y, nz - 1);
-        on[5] = z < nz - 1 || !k.bc[2];
-        q[5] = z < nz - 1 ? o + sz : split_idx(k, x, y, 0);
-    }
+    constexpr int NF = SorIdx<LAT>::NF;
     // diag = W_n + sum_f w_f, off = sum_f w_f chi_f over the faces present (a wall
     // face carries no flux), w_f = (Dc/2) (W_n + W_f)/2, for both systems at once.
     // FP32: each face's pairs are loaded as it is accumulated; FP64 (16-byte pairs):
-    // all faces are loaded first (measured faster in each mode; same arithmetic).
-    const V2<R> Wn = ld(a.w, n), c0 = ld((const V2<R> *)a.chi, n), rhs = ld(a.rhs, n);
+    // all faces are loaded first (measured faster in each mode; same arithmetic), but not
+    // in the persistent solve, whose registers would then allow half the wavefronts.
+    const auto chi = [&](uint32_t j) { return DEV ? ld_dev((const V2<R> *)a.chi, j) : ld((const V2<R> *)a.chi, j); };
+    const V2<R> Wn = ld(a.w, r.n), c0 = chi(r.n), rhs = ld(a.rhs, r.n);
     R dP = Wn.x, oP = 0, dF = Wn.y, oF = 0;
     const auto face = [&](const V2<R> &Wf, const V2<R> &cf) {
         const R wP = a.hdP * (R(0.5) * (Wn.x + Wf.x)), wF = a.hdF * (R(0.5) * (Wn.y + Wf.y));
@@ -1156,20 +1169,20 @@ __device__ __forceinline__ void sor_node(const KP<typename P::R> &k, const SorOp
         dF += wF;
         oF += wF * cf.y;
     };
-    if constexpr (sizeof(R) == 8) {
+    if constexpr (sizeof(R) == 8 && !DEV) {
         V2<R> Wf[NF], cf[NF];
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
-            Wf[f] = on[f] ? ld(a.w, q[f]) : V2<R>{R(0), R(0)};
-            cf[f] = on[f] ? ld((const V2<R> *)a.chi, q[f]) : V2<R>{R(0), R(0)};
+            Wf[f] = r.on[f] ? ld(a.w, r.q[f]) : V2<R>{R(0), R(0)};
+            cf[f] = r.on[f] ? chi(r.q[f]) : V2<R>{R(0), R(0)};
         }
 #pragma unroll
         for (int f = 0; f < NF; ++f)
-            if (on[f]) face(Wf[f], cf[f]);
+            if (r.on[f]) face(Wf[f], cf[f]);
     } else {
 #pragma unroll
         for (int f = 0; f < NF; ++f)
-            if (on[f]) face(ld(a.w, q[f]), ld((const V2<R> *)a.chi, q[f]));
+            if (r.on[f]) face(ld(a.w, r.q[f]), chi(r.q[f]));
     }
     // the pre-update residual |rhs - (diag chi - off)| and |rhs| feed the maxima; a
     // converged system keeps its value
@@ -1184,28 +1197,92 @@ __device__ __forceinline__ void sor_node(const KP<typename P::R> &k, const SorOp
         bloc[1] = fmax(bloc[1], fabs(rhs.y));
         v.y = (R(1) - a.om) * c0.y + a.om * (rhs.y + oF) / dF;
     }
-    st(a.chi, n, v);
+    if constexpr (DEV) st_dev(a.chi, r.n, v);
+    else st(a.chi, r.n, v);
 }
 
-// One tile of a colour half-sweep: 256 consecutive entries of the colour's index
-// space (i, y, z), i fastest, with x = 2 i + parity. A wavefront spans one row of
-// 64 same-colour nodes or, on narrow grids, runs on into the next rows, so no lane
-// idles at the end of a row. SEAM: the grid has seam classes (the test costs
-// registers, so grids without are served by a variant without it).
-template <int LAT, class P, bool SEAM>
+// A row of the persistent solve with everything that does not change from sweep to sweep kept
+// in registers, the own iterate too (no one else writes it): same arithmetic as sor_node.
+template <int LAT, class P> struct SorRow {
+    using R = typename P::R;
+    static constexpr int NF = SorIdx<LAT>::NF;
+    uint32_t n, q[NF];
+    V2<R> w[NF], d, rhs, c;
+    bool live;
+
+    __device__ __forceinline__ void load(const KP<R> &k, const SorOps<R> &a, uint32_t L, int color)
+    {
+        live = L < k.hn;
+        if (!live) return;
+        const uint32_t row = udiv(L, k.hx, k.inv_hx);
+        const uint32_t z = Lat<LAT>::D == 3 ? udiv(row, (uint32_t)k.ny, k.inv_ny) : 0u;
+        const int y = (int)(row - z * (uint32_t)k.ny);
+        const int x = 2 * (int)(L - row * k.hx) + ((y + (int)z + color) & 1);
+        live = x < k.nx && !on_seam<Lat<LAT>::D>(k, x, y, z);
+        if (!live) return;
+        const SorIdx<LAT> r = sor_idx<LAT>(k, L, x, y, (int)z, color);
+        n = r.n;
+        const V2<R> Wn = ld(a.w, n);
+        c = ld((const V2<R> *)a.chi, n);
+        rhs = ld(a.rhs, n);
+        d = Wn;
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            // no face: the node itself with weight zero
+            q[f] = r.on[f] ? r.q[f] : n;
+            const V2<R> Wf = ld(a.w, q[f]);
+            const R wP = a.hdP * (R(0.5) * (Wn.x + Wf.x)), wF = a.hdF * (R(0.5) * (Wn.y + Wf.y));
+            if (r.on[f]) {
+                d.x += wP;
+                d.y += wF;
+            }
+            w[f] = r.on[f] ? V2<R>{wP, wF} : V2<R>{R(0), R(0)};
+        }
+    }
+    __device__ __forceinline__ void update(const SorOps<R> &a, const bool *conv, R *rloc, R *bloc)
+    {
+        if (!live) return;
+        V2<R> cf[NF];
+#pragma unroll
+        for (int f = 0; f < NF; ++f) cf[f] = ld_dev((const V2<R> *)a.chi, q[f]);
+        R oP = 0, oF = 0;
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            oP += w[f].x * cf[f].x;
+            oF += w[f].y * cf[f].y;
+        }
+        if (!conv[0]) {
+            rloc[0] = fmax(rloc[0], fabs(rhs.x - (d.x * c.x - oP)));
+            bloc[0] = fmax(bloc[0], fabs(rhs.x));
+            c.x = (R(1) - a.om) * c.x + a.om * (rhs.x + oP) / d.x;
+        }
+        if (!conv[1]) {
+            rloc[1] = fmax(rloc[1], fabs(rhs.y - (d.y * c.y - oF)));
+            bloc[1] = fmax(bloc[1], fabs(rhs.y));
+            c.y = (R(1) - a.om) * c.y + a.om * (rhs.y + oF) / d.y;
+        }
+        st_dev(a.chi, n, c);
+    }
+};
+
+// One tile of a colour half-sweep: as many consecutive entries of the colour's index
+// space (i, y, z), i fastest, with x = 2 i + parity, as the workgroup has threads. A
+// wavefront spans one row of 64 same-colour nodes or, on narrow grids, runs on into
+// the next rows, so no lane idles at the end of a row. SEAM: the grid has seam classes
+// (the test costs registers, so grids without are served by a variant without it).
+template <int LAT, class P, bool SEAM, int NT = 256, bool DEV = false>
 __device__ __forceinline__ void sor_tile(const KP<typename P::R> &k, const SorOps<typename P::R> &a, int tile,
                                          int color, const bool *conv, typename P::R *rloc, typename P::R *bloc)
 {
-    const uint32_t hx = (uint32_t)(k.nx + 1) >> 1;
-    const uint32_t L = (uint32_t)tile * 256u + threadIdx.x;
-    if (L >= hx * (uint32_t)k.ny * (uint32_t)k.nz) return;
-    const uint32_t row = udiv(L, hx, k.inv_hx);
-    const uint32_t z = udiv(row, (uint32_t)k.ny, k.inv_ny);
+    const uint32_t L = (uint32_t)tile * (uint32_t)NT + threadIdx.x;
+    if (L >= k.hn) return;
+    const uint32_t row = udiv(L, k.hx, k.inv_hx);
+    const uint32_t z = Lat<LAT>::D == 3 ? udiv(row, (uint32_t)k.ny, k.inv_ny) : 0u;
     const int y = (int)(row - z * (uint32_t)k.ny);
-    const int x = 2 * (int)(L - row * hx) + ((y + (int)z + color) & 1);
+    const int x = 2 * (int)(L - row * k.hx) + ((y + (int)z + color) & 1);
     if (x >= k.nx) return;
     if (SEAM && on_seam<Lat<LAT>::D>(k, x, y, z)) return;   // updated with its seam class
-    sor_node<LAT, P>(k, a, x, y, z, conv, rloc, bloc);
+    sor_node<LAT, P, DEV>(a, sor_idx<LAT>(k, L, x, y, (int)z, color), conv, rloc, bloc);
 }
 
 // Seam classes. On a periodic axis of odd extent the parity colouring wraps onto
@@ -1217,8 +1294,8 @@ __device__ __forceinline__ void sor_tile(const KP<typename P::R> &k, const SorOp
 // each half-sweep is free of races and the order of all updates is fixed.
 // Index space of an instance: for each seam axis a in turn, its last plane, the
 // other two axes in increasing order with the lower one fastest.
-template <int LAT, class P>
-__device__ __forceinline__ void sor_seam_node(const KP<typename P::R> &k, const SorOps<typename P::R> &a, long long t,
+template <int LAT, class P, bool DEV = false>
+__device__ __forceinline__ void sor_seam_node(const KP<typename P::R> &k, const SorOps<typename P::R> &a, uint32_t t,
                                               int level, int color, const bool *conv, typename P::R *rloc,
                                               typename P::R *bloc)
 {
@@ -1228,7 +1305,7 @@ __device__ __forceinline__ void sor_seam_node(const KP<typename P::R> &k, const 
 #pragma unroll
     for (int a = 0; a < D; ++a) {
         if (axis >= 0 || !((k.seam >> a) & 1)) continue;
-        const long long plane = k.N / ext[a];
+        const uint32_t plane = (uint32_t)(a == 0 ? k.ny * k.nz : a == 1 ? k.nx * k.nz : k.nx * k.ny);
         if (t < plane) axis = a;
         else t -= plane;
     }
@@ -1236,8 +1313,8 @@ __device__ __forceinline__ void sor_seam_node(const KP<typename P::R> &k, const 
     const int b0 = axis == 0 ? 1 : 0, b1 = axis == 2 ? 1 : 2;
     int c[3];
     c[axis] = ext[axis] - 1;
-    c[b0] = (int)(t % ext[b0]);
-    c[b1] = (int)(t / ext[b0]);
+    c[b1] = (int)udiv(t, (uint32_t)ext[b0], b0 == 0 ? k.inv_nx : k.inv_ny);
+    c[b0] = (int)t - c[b1] * ext[b0];
     int lv = 0, lowest = -1;
 #pragma unroll
     for (int a = 0; a < D; ++a)
@@ -1247,7 +1324,8 @@ __device__ __forceinline__ void sor_seam_node(const KP<typename P::R> &k, const 
         }
     // a node on several last planes is visited once, from its lowest seam axis
     if (lv != level || lowest != axis || ((c[0] + c[1] + c[2]) & 1) != color) return;
-    sor_node<LAT, P>(k, a, c[0], c[1], c[2], conv, rloc, bloc);
+    const uint32_t L = (uint32_t)(c[0] >> 1) + k.hx * (uint32_t)(c[1] + k.ny * c[2]);
+    sor_node<LAT, P, DEV>(a, sor_idx<LAT>(k, L, c[0], c[1], c[2], color), conv, rloc, bloc);
 }
 
 // Number of tiles of one colour of a half-sweep.
@@ -1282,7 +1360,11 @@ __global__ __launch_bounds__(256) void k_sor(KP<typename P::R> k, int color, int
     if (sweep == 0) block_max_to_slots(bloc[0], bloc[1], k.fld.sorres, RMAX_IDX);
 }
 
-// The same half-sweep for a batch of instances: one workgroup per tile of one instance.
+// The same half-sweep for a batch of instances: one workgroup per SORB_TILES tiles of one
+// instance, which share its look-up, its test and its reduction: a chain of dependent loads
+// longer than the update itself (64 columns of 1e5 nodes: 61 us with one tile a workgroup,
+// 45 with four, 45 with eight).
+constexpr int SORB_TILES = 4;
 template <int LAT, class P, bool SEAM>
 __global__ __launch_bounds__(256) void kb_sor(const KP<typename P::R> *tab, const int *prefix, int ninst, StepArgs sa,
                                              int color, int sweep)
@@ -1295,100 +1377,382 @@ __global__ __launch_bounds__(256) void kb_sor(const KP<typename P::R> *tab, cons
     sor_conv<LAT, P>(k, color, sweep, conv);
     if (conv[0] && conv[1]) return;
     R rloc[2] = {0, 0}, bloc[2] = {0, 0};
-    sor_tile<LAT, P, SEAM>(k, sor_ops(k, sa), local, color, conv, rloc, bloc);
+    const SorOps<R> a = sor_ops(k, sa);
+    for (int t = 0; t < SORB_TILES; ++t)
+        sor_tile<LAT, P, SEAM>(k, a, local * SORB_TILES + t, color, conv, rloc, bloc);
     block_max_to_slots(conv[0] ? R(-1) : rloc[0], conv[1] ? R(-1) : rloc[1], k.fld.sorres, 2 * sweep + color);
     if (sweep == 0) block_max_to_slots(bloc[0], bloc[1], k.fld.sorres, RMAX_IDX);
 }
 
-// Sweeps of a batch past the third usually find most instances converged, and one
-// workgroup per tile of every instance then costs a dispatch of every tile. There,
-// kb_sor_live first records per instance (one wavefront each) which systems the
-// coming half-sweep still updates, and kb_sor_late runs that half-sweep on a narrow
-// grid over the live instances only: each workgroup strides over the tiles of each
-// live instance and feeds that instance's residual maxima once. The updates of a
-// colour half-sweep do not depend on their order and the maxima not on their
-// grouping, so every instance gets the result of kb_sor.
-template <int LAT, class P>
-__global__ __launch_bounds__(64) void kb_sor_live(const KP<typename P::R> *tab, int color, int sweep)
+// ---- persistent solve ----
+//
+// The sweeps from `first` on in one launch: the workgroups meet at a barrier after every
+// colour half-sweep (and seam half-sweep) instead of at a launch boundary, and leave as
+// soon as both systems have converged. Same updates in the same red-black order as the
+// half-sweep launches, so the same result.
+//
+// The barrier never waits for a workgroup that is not running: the group is made of
+// those that have drawn a ticket by the time the last expected one does, or the first
+// one has waited long enough; whoever comes later leaves at once, and the tiles are
+// dealt to the members there are. Other launches on the device, however many streams
+// they are on, can therefore only make the group smaller.
+//
+// What bounds it: the latency of a phase, not work (an update is some 100 instructions):
+// iterates written and read through the device's point of coherence, the flags there and
+// back, and the update between them. Hence device-scope accesses for the iterates alone
+// (fences of that scope around plain ones cost 8 us a barrier with 256 workgroups, these 2
+// to 4), few large workgroups, and no atomic counter.
+constexpr int REST_T = 512;            // threads of a workgroup
+constexpr int REST_NW = REST_T / 64;   // its wavefronts
+static_assert((REST_NW & (REST_NW - 1)) == 0 && 4 * REST_NW <= 64, "one wavefront reduces four values of each");
+
+// A group: this workgroup's index, the number of members (0: not one of them), phases passed.
+struct SorGroup {
+    SorSync *s;
+    uint32_t rank, members, phase;
+};
+
+// LDS of the persistent solve.
+struct SorShared {
+    uint32_t box[2], bits[REST_NW];
+    double red[4][REST_NW], lim[2];
+};
+
+// Join the group of at most `want` workgroups (every workgroup that takes part calls this,
+// all of its threads).
+__device__ __forceinline__ SorGroup sor_enrol(SorSync *s, uint32_t want, SorShared &sh)
 {
-    const KP<typename P::R> &k = tab[blockIdx.x];
-    bool conv[2];
-    sor_conv<LAT, P>(k, color, sweep, conv);
-    if (threadIdx.x == 0) k.fld.sc->sor_live = (conv[0] ? 0u : 1u) | (conv[1] ? 0u : 2u);
+    if (threadIdx.x == 0) {
+        uint32_t m = 0;
+        const uint32_t t = __hip_atomic_fetch_add(&s->tickets, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!(t & SYNC_CLOSED)) {
+            if (t == want - 1u) {   // everybody is here
+                m = want;
+                st_dev(&s->members, m);
+            } else {
+                // the first one closes the group after some ten reads (a few us); it is
+                // running, so the others' wait for the number of members ends
+                for (int i = 0; (m = ld_dev(&s->members)) == 0u; ++i) {
+                    __builtin_amdgcn_s_sleep(1);
+                    if (t != 0u || i != 10) continue;
+                    const uint32_t n =
+                        __hip_atomic_fetch_or(&s->tickets, SYNC_CLOSED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (n < want) st_dev(&s->members, n);   // else the last one says so
+                }
+            }
+        }
+        sh.box[0] = t;
+        sh.box[1] = m;
+    }
+    __syncthreads();
+    const SorGroup g{s, sh.box[0], sh.box[1], 0u};
+    __syncthreads();   // box is written again
+    return g;
 }
-template <int LAT, class P, bool SEAM>
-__global__ __launch_bounds__(256) void kb_sor_late(const KP<typename P::R> *tab, const int *prefix, int ninst,
-                                                  StepArgs sa, int color, int sweep)
+
+// End of a phase: the residuals of this workgroup's rows are recorded and the group meets.
+// Returns the systems (bit 0 psi, bit 1 phi) that some member leaves above the tolerance.
+// Every member stores one flag and reads all of them: two trips to the device's point of
+// coherence, where a counter would take three and a chain of additions. A member may be
+// one phase ahead of another, never two, hence the two sets of flags.
+template <class R>
+__device__ __forceinline__ uint32_t sor_meet(const KP<R> &k, SorGroup &g, int s, int color, uint32_t open,
+                                             const R *rloc, const R *bloc, double lim0, double lim1, SorShared &sh)
 {
-    using R = typename P::R;
-    __shared__ uint32_t live[64];
-    __shared__ unsigned long long lmask;
-    for (int c0 = 0; c0 < ninst; c0 += 64) {
-        if (threadIdx.x < 64) {
-            const uint32_t v = c0 + (int)threadIdx.x < ninst ? tab[c0 + threadIdx.x].fld.sc->sor_live : 0u;
-            live[threadIdx.x] = v;
-            const unsigned long long m = __ballot(v != 0u);
-            if (threadIdx.x == 0) lmask = m;
+    g.phase += 1u;
+    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    // this wavefront's iterates have reached device scope before the workgroup reports
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (s > 0) {
+        // against a known tolerance one row above it decides: a slot gets the residual of any
+        // such row instead of the maximum
+        uint32_t bits = 0u;
+#pragma unroll
+        for (int fi = 0; fi < 2; ++fi) {
+            const double r = (double)rloc[fi];
+            const unsigned long long b = __ballot(((open >> fi) & 1u) && !(r <= (fi ? lim1 : lim0)));
+            if (b == 0ull) continue;
+            bits |= 1u << fi;
+            if (lane == __builtin_ctzll(b))
+                st_dev(res_slot(k.fld.sorres, fi, 2 * s + color, (int)(g.rank % RSLOTS)),
+                       (unsigned long long)__double_as_longlong(r));
         }
-        __syncthreads();
-        unsigned long long m = lmask;
-        while (m) {
-            const int i = __builtin_ctzll(m);
-            m &= m - 1;
-            const int inst = c0 + i;
-            const int nt = prefix[inst + 1] - prefix[inst];
-            if ((int)blockIdx.x >= nt) continue;
-            const KP<R> &k = tab[inst];
-            const uint32_t v = live[i];
-            const bool conv[2] = {(v & 1u) == 0u, (v & 2u) == 0u};
-            const SorOps<R> a = sor_ops(k, sa);
-            R rloc[2] = {0, 0}, bloc[2] = {0, 0};
-            for (int t = blockIdx.x; t < nt; t += gridDim.x) sor_tile<LAT, P, SEAM>(k, a, t, color, conv, rloc, bloc);
-            block_max_to_slots(conv[0] ? R(-1) : rloc[0], conv[1] ? R(-1) : rloc[1], k.fld.sorres, 2 * sweep + color);
+        if (lane == 0) sh.bits[wv] = bits;
+    } else {
+        // sweep 0: maxima of the residuals and of |rhs|
+        const double r0 = (double)wave_max(rloc[0]), r1 = (double)wave_max(rloc[1]);
+        const double b0 = (double)wave_max(bloc[0]), b1 = (double)wave_max(bloc[1]);
+        if (lane == 0) {
+            sh.red[0][wv] = r0;
+            sh.red[1][wv] = r1;
+            sh.red[2][wv] = b0;
+            sh.red[3][wv] = b1;
+            sh.bits[wv] = 3u;
         }
-        __syncthreads();   // live and lmask are rewritten for the next 64 instances
+    }
+    __syncthreads();
+    if (wv == 0) {
+        if (s == 0) {
+            // lane REST_NW i + w: quantity i of wavefront w
+            const int q = lane / REST_NW;
+            double m = q < 4 ? sh.red[q][lane % REST_NW] : 0.0;
+#pragma unroll
+            for (int off = REST_NW / 2; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
+            if (lane % REST_NW == 0 && q < 4)
+                atomic_max_nonneg(res_slot(k.fld.sorres, q & 1, q < 2 ? color : RMAX_IDX, (int)(g.rank % RSLOTS)), m);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        }
+        const uint32_t w = lane < REST_NW ? sh.bits[lane] : 0u;
+        const uint32_t mine = (__ballot((w & 1u) != 0u) ? 1u : 0u) | (__ballot((w & 2u) != 0u) ? 2u : 0u);
+        uint32_t *f = g.s->flag[g.phase & 1u];
+        if (lane == 0) st_dev(&f[g.rank], g.phase << 2 | mine);
+        uint32_t any = 0u;
+        for (uint32_t m = (uint32_t)lane; m < g.members; m += 64u) {
+            uint32_t v;
+            while (((v = ld_dev(&f[m])) >> 2) < g.phase) __builtin_amdgcn_s_sleep(0);
+            any |= v;
+        }
+        const uint32_t u = (__ballot((any & 1u) != 0u) ? 1u : 0u) | (__ballot((any & 2u) != 0u) ? 2u : 0u);
+        if (lane == 0) sh.box[0] = u;
+    }
+    __syncthreads();
+    asm volatile("" ::: "memory");
+    return sh.box[0];
+}
+
+// Nodes of the seam index space.
+template <class R> __device__ __forceinline__ uint32_t seam_nodes(const KP<R> &k)
+{
+    return (k.seam & 1 ? (uint32_t)(k.ny * k.nz) : 0u) + (k.seam & 2 ? (uint32_t)(k.nx * k.nz) : 0u) +
+           (k.seam & 4 ? (uint32_t)(k.nx * k.ny) : 0u);
+}
+
+// The last seam levels (both in 2-D, where they are a row, a column and their corner; the edges
+// and the corner in 3-D) by one workgroup, with its own barrier between their half-sweeps.
+template <int LAT, class P, int NT, bool DEV>
+__device__ __forceinline__ void sor_seam_tail(const KP<typename P::R> &k, const SorOps<typename P::R> &a,
+                                              const bool *conv, typename P::R *rloc, typename P::R *bloc)
+{
+    const int levels = __builtin_popcount((unsigned)k.seam);
+    if constexpr (Lat<LAT>::D == 2) {
+        const uint32_t S = seam_nodes(k);
+        for (int h = 2; h < 2 + 2 * levels; ++h) {
+            for (uint32_t t = threadIdx.x; t < S; t += NT)
+                sor_seam_node<LAT, P, DEV>(k, a, t, h >> 1, h & 1, conv, rloc, bloc);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+        }
+    } else {
+        // the edges along z, y and x (of the seam axis pairs xy, xz and yz) one after another,
+        // the corner from the first of them
+        const uint32_t ez = (k.seam & 3) == 3 ? (uint32_t)k.nz : 0u, ey = (k.seam & 5) == 5 ? (uint32_t)k.ny : 0u,
+                       ex = (k.seam & 6) == 6 ? (uint32_t)k.nx : 0u;
+        for (int h = 4; h < 2 + 2 * levels; ++h) {
+            for (uint32_t t = threadIdx.x; t < ez + ey + ex; t += NT) {
+                int x = k.nx - 1, y = k.ny - 1, z = k.nz - 1;
+                bool corner = levels == 3;
+                if (t < ez) corner = corner && (int)t == z, z = (int)t;
+                else if (t < ez + ey) corner = corner && (int)(t - ez) == y, y = (int)(t - ez);
+                else corner = corner && (int)(t - ez - ey) == x, x = (int)(t - ez - ey);
+                if ((h >> 1) != (corner ? 3 : 2) || (corner && t >= ez) || ((x + y + z) & 1) != (h & 1)) continue;
+                const uint32_t L = (uint32_t)(x >> 1) + k.hx * (uint32_t)(y + k.ny * z);
+                sor_node<LAT, P, DEV>(a, sor_idx<LAT>(k, L, x, y, z, h & 1), conv, rloc, bloc);
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+        }
     }
 }
 
-// One parity half-sweep of one seam level (one thread per entry of the seam index space).
+// One phase of the persistent solve over this member's share of its rows, then the meeting: the
+// half-sweep `color` of sweep s (lv 0), of seam level lv, or (lv < 0) the last seam levels.
+template <int LAT, class P, bool SEAM>
+__device__ __forceinline__ uint32_t sor_phase(const KP<typename P::R> &k, const SorOps<typename P::R> &a, SorGroup &g,
+                                              int s, int color, int lv, uint32_t open, double lim0, double lim1,
+                                              SorRow<LAT, P> *row, SorShared &sh)
+{
+    using R = typename P::R;
+    const bool conv[2] = {(open & 1u) == 0u, (open & 2u) == 0u};
+    R rloc[2] = {0, 0}, bloc[2] = {0, 0};
+    if ((!SEAM || lv == 0) && row) {
+        row->update(a, conv, rloc, bloc);
+    } else if (!SEAM || lv == 0) {
+        const uint32_t nt = (k.hn + REST_T - 1u) / REST_T;
+        for (uint32_t t = g.rank; t < nt; t += g.members)
+            sor_tile<LAT, P, SEAM, REST_T, true>(k, a, (int)t, color, conv, rloc, bloc);
+    } else if (lv > 0) {
+        const uint32_t S = seam_nodes(k);
+        for (uint32_t t = g.rank * REST_T + threadIdx.x; t < S; t += g.members * REST_T)
+            sor_seam_node<LAT, P, true>(k, a, t, lv, color, conv, rloc, bloc);
+    } else if (g.rank == 0u) {
+        // with seam classes the test is over a whole sweep: either colour's slot will do
+        sor_seam_tail<LAT, P, REST_T, true>(k, a, conv, rloc, bloc);
+    }
+    return sor_meet(k, g, s, color, open, rloc, bloc, lim0, lim1, sh);
+}
+
+// Systems still open before sweep `first`, from the launches that did the sweeps before it.
 template <int LAT, class P>
-__global__ __launch_bounds__(256) void k_sor_seam(KP<typename P::R> k, int level, int color, int sweep)
+__device__ __forceinline__ uint32_t sor_open(const KP<typename P::R> &k, int first, SorShared &sh)
+{
+    if (first == 0) return 3u;
+    if (threadIdx.x < 64) {
+        bool conv[2];
+        sor_conv<LAT, P>(k, 0, first, conv);
+        if (threadIdx.x == 0) sh.box[0] = (conv[0] ? 0u : 1u) | (conv[1] ? 0u : 2u);
+    }
+    __syncthreads();
+    const uint32_t open = sh.box[0];
+    __syncthreads();
+    return open;
+}
+
+// Sweeps first .. nsw - 1 of one instance by the group, with `open` systems left to solve. ROWS:
+// a member has one tile of each colour at most, and keeps its rows in registers.
+template <int LAT, class P, bool SEAM, bool ROWS>
+__device__ __forceinline__ void sor_sweeps_as(const KP<typename P::R> &k, const StepArgs &sa, SorGroup &g, int first,
+                                              int nsw, uint32_t open, SorShared &sh)
+{
+    using R = typename P::R;
+    const SorOps<R> a = sor_ops(k, sa);
+    SorRow<LAT, P> red, black;
+    if constexpr (ROWS) {
+        red.load(k, a, g.rank * REST_T + threadIdx.x, 0);
+        black.load(k, a, g.rank * REST_T + threadIdx.x, 1);
+    }
+    const auto phase = [&](int s, int color, int lv, double lim0, double lim1) {
+        return sor_phase<LAT, P, SEAM>(k, a, g, s, color, lv, open, lim0, lim1,
+                                       !ROWS ? nullptr : color == 0 ? &red : &black, sh);
+    };
+    double lim0 = 0.0, lim1 = 0.0;
+    for (int s = first; s < nsw; ++s) {
+        if (s == 1 || (s == first && s > 0)) {
+            // max |rhs| of sweep 0 is complete: the tolerances. Where the whole sweep is tested,
+            // sweep 0 ran without them: test what it recorded.
+            __syncthreads();   // box has been read
+            if (threadIdx.x < 64) {
+                uint32_t o = 0u;
+#pragma unroll
+                for (int fi = 0; fi < 2; ++fi) {
+                    const auto slot = [&](int e) { return bits_to_double(ld_dev(res_slot(k.fld.sorres, fi, e, (int)threadIdx.x))); };
+                    const double r = fmax(slot(0), slot(1)), lim = (double)k.tol * wave_max(slot(RMAX_IDX));
+                    if (__ballot(!(r <= lim))) o |= 1u << fi;
+                    if (threadIdx.x == 0) sh.lim[fi] = lim;
+                }
+                if (threadIdx.x == 0) sh.box[0] = !k.sor_exact && s == 1 ? o : 3u;
+            }
+            __syncthreads();
+            lim0 = sh.lim[0];
+            lim1 = sh.lim[1];
+            open &= sh.box[0];
+            if (open == 0u) return;
+        }
+        // systems left open by the phases of this sweep (omega = 1 without seam classes: the
+        // red residual alone is the whole residual, and its black half is then skipped)
+        uint32_t left = phase(s, 0, 0, lim0, lim1);
+        if (k.sor_exact && s > 0) {
+            open &= left;
+            if (open == 0u) return;
+        }
+        left |= phase(s, 1, 0, lim0, lim1);
+        if constexpr (SEAM) {
+            constexpr int LV0 = Lat<LAT>::D - 1;   // first of the levels that one workgroup takes
+            for (int h = 2; h < 2 * LV0; ++h) left |= phase(s, h & 1, h >> 1, lim0, lim1);
+            if (__builtin_popcount((unsigned)k.seam) >= LV0) left |= phase(s, 0, -1, lim0, lim1);
+        }
+        if (!k.sor_exact && s > 0) {
+            open &= left;
+            if (open == 0u) return;
+        }
+    }
+}
+template <int LAT, class P, bool SEAM, bool ROWS>
+__device__ __forceinline__ void sor_sweeps(const KP<typename P::R> &k, const StepArgs &sa, SorGroup &g, int first,
+                                           int nsw, uint32_t open, SorShared &sh)
+{
+    if constexpr (ROWS)
+        if (k.hn <= g.members * REST_T) {
+            sor_sweeps_as<LAT, P, SEAM, true>(k, sa, g, first, nsw, open, sh);
+            return;
+        }
+    sor_sweeps_as<LAT, P, SEAM, false>(k, sa, g, first, nsw, open, sh);
+}
+
+// near: only the workgroups of one residue mod 8 take part. The hardware deals workgroups to
+// the eight XCDs in turn, so these share an L2.
+template <int LAT, class P, bool SEAM, bool ROWS>
+__global__ __launch_bounds__(REST_T, ROWS ? 2 : 4) void k_sor_rest(KP<typename P::R> k, int first, int nsw, int near)
+{
+    __shared__ SorShared sh;
+    if (near && (blockIdx.x & 7u) != 0u) return;
+    const uint32_t open = sor_open<LAT, P>(k, first, sh);
+    if (open == 0u) return;   // the usual case after some sweeps by launches
+    SorGroup g = sor_enrol(k.fld.sync, near ? gridDim.x >> 3 : gridDim.x, sh);
+    if (g.members == 0u) return;
+    sor_sweeps<LAT, P, SEAM, ROWS>(k, step_args(k), g, first, nsw, open, sh);
+}
+
+// Batch: `groups` groups of `per` workgroups (group i on the XCD i mod 8), group i solving the
+// instances i, i + groups, ... one after another: the pair arrays of an instance stay in
+// that XCD's L2 from phase to phase, and while one group meets another one works.
+template <int LAT, class P, bool SEAM, bool ROWS>
+__global__ __launch_bounds__(REST_T, ROWS ? 2 : 4) void kb_sor_rest(const KP<typename P::R> *tab, int ninst, StepArgs sa, int first,
+                                                     int nsw, int groups, int per)
+{
+    __shared__ SorShared sh;
+    const int i0 = (int)(blockIdx.x >> 3) / per * 8 + (int)(blockIdx.x & 7u);
+    if (i0 >= groups) return;
+    SorGroup g{nullptr, 0u, 0u, 0u};
+    for (int i = i0; i < ninst; i += groups) {
+        const uint32_t open = sor_open<LAT, P>(tab[i], first, sh);
+        if (open == 0u) continue;
+        if (!g.s) {
+            g = sor_enrol(tab[i0].fld.sync, (uint32_t)per, sh);
+            if (g.members == 0u) return;
+        }
+        sor_sweeps<LAT, P, SEAM, ROWS>(tab[i], sa, g, first, nsw, open, sh);
+        __syncthreads();
+    }
+}
+
+// One parity half-sweep of one seam level (one thread per entry of the seam index space), or
+// (level < 0, one workgroup) the last levels.
+template <int LAT, class P>
+__device__ __forceinline__ void sor_seam_body(const KP<typename P::R> &k, const StepArgs &sa, uint32_t local, int level,
+                                              int color, int sweep)
 {
     using R = typename P::R;
     bool conv[2];
     sor_conv<LAT, P>(k, color, sweep, conv);
     if (conv[0] && conv[1]) return;
     R rloc[2] = {0, 0}, bloc[2] = {0, 0};
-    sor_seam_node<LAT, P>(k, sor_ops(k, step_args(k)), (long long)blockIdx.x * 256 + threadIdx.x, level, color, conv,
-                          rloc, bloc);
+    const SorOps<R> a = sor_ops(k, sa);
+    if (level < 0) sor_seam_tail<LAT, P, 256, false>(k, a, conv, rloc, bloc);
+    else sor_seam_node<LAT, P>(k, a, local * 256u + threadIdx.x, level, color, conv, rloc, bloc);
     block_max_to_slots(conv[0] ? R(-1) : rloc[0], conv[1] ? R(-1) : rloc[1], k.fld.sorres, 2 * sweep + color);
     if (sweep == 0) block_max_to_slots(bloc[0], bloc[1], k.fld.sorres, RMAX_IDX);
 }
+template <int LAT, class P>
+__global__ __launch_bounds__(256) void k_sor_seam(KP<typename P::R> k, int level, int color, int sweep)
+{
+    sor_seam_body<LAT, P>(k, step_args(k), blockIdx.x, level, color, sweep);
+}
 
-// The same for a batch: instance i owns workgroups prefix[i] .. prefix[i+1]-1.
+// The same for a batch: instance i owns workgroups prefix[i] .. prefix[i+1]-1 (prefix null: one
+// workgroup, the last levels).
 template <int LAT, class P>
 __global__ __launch_bounds__(256) void kb_sor_seam(const KP<typename P::R> *tab, const int *prefix, int ninst,
                                                   StepArgs sa, int level, int color, int sweep)
 {
-    using R = typename P::R;
-    int inst, local;
-    batch_tile(prefix, ninst, inst, local);
-    const KP<R> &k = tab[inst];
-    bool conv[2];
-    sor_conv<LAT, P>(k, color, sweep, conv);
-    if (conv[0] && conv[1]) return;
-    R rloc[2] = {0, 0}, bloc[2] = {0, 0};
-    sor_seam_node<LAT, P>(k, sor_ops(k, sa), (long long)local * 256 + threadIdx.x, level, color, conv, rloc, bloc);
-    block_max_to_slots(conv[0] ? R(-1) : rloc[0], conv[1] ? R(-1) : rloc[1], k.fld.sorres, 2 * sweep + color);
-    if (sweep == 0) block_max_to_slots(bloc[0], bloc[1], k.fld.sorres, RMAX_IDX);
+    int inst = (int)blockIdx.x, local = 0;
+    if (prefix) batch_tile(prefix, ninst, inst, local);
+    if (!tab[inst].seam) return;
+    sor_seam_body<LAT, P>(tab[inst], sa, (uint32_t)local, level, color, sweep);
 }
 
-// Sweep counts of the last solve; LBFD_ESOR when a system never met its tolerance.
-// One wavefront: lane l reads residual slot l. Afterwards it clears the slots of
-// every half-sweep and of the |rhs| maxima for the next step.
-// One wavefront: the sweep counts and max |rhs| of the last solve, and LBFD_ESOR when a
-// system did not converge within the nsw sweeps launched.
-template <class R> __device__ __forceinline__ void sor_record(const KP<R> &k, int nsw)
+// One wavefront (lane l reads residual slot l): the sweep counts K[2] and max |rhs| of the
+// last solve, and LBFD_ESOR when a system did not converge within its nsw sweeps.
+template <class R> __device__ __forceinline__ void sor_record(const KP<R> &k, int nsw, int *counts)
 {
     DevScalars *sc = k.fld.sc;
     const int lane = threadIdx.x & 63;
@@ -1431,14 +1795,18 @@ template <class R> __device__ __forceinline__ void sor_record(const KP<R> &k, in
         if (lane == 0) {
             sc->rmax[fi] = (unsigned long long)__double_as_longlong(rm);
             sc->sweeps[fi] = K;
+            counts[fi] = K;
             if (!ok && sc->status == 0) sc->status = LBFD_ESOR;
         }
     }
 }
-// batch: one wavefront per instance
 // Clears the residual and |rhs| slots (set-up, before the first step).
-template <class R> __global__ void k_sor_clear(KP<R> k, int nsw) { sor_slots_clear(k.fld.sorres, nsw); }
-
+// An idle meeting place for the persistent solve (at creation).
+__global__ void k_sync_clear(SorSync *s)
+{
+    for (int i = threadIdx.x; i < (int)(sizeof(SorSync) / 4); i += blockDim.x) ((uint32_t *)s)[i] = 0u;
+}
+template <class R> __global__ void k_sor_clear(KP<R> k, int nsw) { sor_slots_clear(k.fld.sorres, k.fld.sync, nsw, nsw); }
 
 // One FD field from FP64 values: psi and phi given as physical values (stored
 // divided by the current scale factor), the AB2 histories as they are.
@@ -1654,11 +2022,13 @@ template <class R> __device__ __forceinline__ void total_final_body(const KP<R> 
     __shared__ double sh[256];
     const int t = threadIdx.x;
     if (nsw > 0) {
-        // after a solve: record its sweeps (first wavefront), then clear its residual
-        // slots for the next one (the total's partial sums read none of them)
-        if (t < 64) sor_record(k, nsw);
+        // after a solve: record its sweeps (first wavefront), then clear the residual slots
+        // it wrote for the next one (a system is updated, and records, in at most one
+        // sweep past its count; the total's partial sums read none of the slots)
+        __shared__ int counts[2];
+        if (t < 64) sor_record(k, nsw, counts);
         __syncthreads();
-        sor_slots_clear(k.fld.sorres, nsw);
+        sor_slots_clear(k.fld.sorres, k.fld.sync, min(counts[0] + 1, nsw), min(counts[1] + 1, nsw));
     }
     double a = 0.0;
     for (long long b = t; b < nblocks; b += 256) a += k.fld.part[b];
@@ -1897,7 +2267,10 @@ struct lbfd_handle {
     int tblocks;        // workgroups of the total-surfactant sum
     int sweeps_launch;
     long long fd_hist;  // FD steps since the state was set (extrapolated guess needs one)
-    int sor_blocks;     // persistent grid of the SOR sweeps
+    int sor_blocks;     // persistent grid of the SOR half-sweep launches
+    int sor_lead;       // sweeps done by half-sweep launches; the persistent solve takes the others
+    int rest_wgs;       // workgroups of the persistent solve
+    bool rest_near;     // they all sit on one XCD
     int seam_tiles;     // workgroups over the seam index space (0: no seam classes)
     int seam_levels;    // seam levels (periodic axes of odd extent)
     bool prof;
@@ -1930,6 +2303,9 @@ struct lbfd_batch {
     int *prefix_seam;   // device: first seam workgroup of each instance (n + 1 entries)
     dim3 grid_node, grid_sor, grid_total, grid_seam;
     int seam_levels;    // most seam levels of any instance
+    int sor_lead;       // as for a single handle, the same for every instance
+    int rest_groups;    // groups of the persistent solve (each takes every rest_groups-th instance)
+    int rest_wgs;       // workgroups of a group
     int rows = BY;      // rows of 64 x per workgroup of the node kernels (every instance)
     StepGraphs graphs;
 };
@@ -1943,7 +2319,7 @@ size_t pop_bytes(int prec) { return prec == LBFD_FP64 ? 8 : prec == LBFD_FP32 ? 
 size_t real_bytes(int prec) { return prec == LBFD_FP64 ? 8 : 4; }
 
 struct Layout {
-    size_t f[2], mac[2], desc, G[2], nrm, u, F, qf, sorres, psi[2], phi[2], Sp, Bp, rhs2, cs2, cw2,
+    size_t f[2], mac[2], desc, G[2], nrm, u, F, qf, sorres, sync, psi[2], phi[2], Sp, Bp, rhs2, cs2, cw2,
         part, sc, obs, total;
 };
 
@@ -1966,6 +2342,7 @@ Layout layout(const lbfd_params *p)
     L.F = take(sr * D * N);
     L.qf = take(sr * D * N);
     L.sorres = take(sizeof(unsigned long long) * 2 * (RMAX_IDX + 1) * RSLOTS * RSTRIDE);
+    L.sync = take(sizeof(SorSync));
     for (int b = 0; b < 2; ++b) L.psi[b] = take(sr * N);
     for (int b = 0; b < 2; ++b) L.phi[b] = take(sr * N);
     L.Sp = take(sr * N);
@@ -2143,6 +2520,7 @@ template <class R> void fill_kp(KP<R> &k, const lbfd_params *p, char *ws, const 
     F.F = (R *)(ws + Lo.F);
     F.qf = (R *)(ws + Lo.qf);
     F.sorres = (unsigned long long *)(ws + Lo.sorres);
+    F.sync = (SorSync *)(ws + Lo.sync);
     F.Sp = (R *)(ws + Lo.Sp);
     F.Bp = (R *)(ws + Lo.Bp);
     F.rhs2 = (V2<R> *)(ws + Lo.rhs2);
@@ -2218,6 +2596,7 @@ static size_t field_count(const lbfd_handle *h, int field)
 
 template <int LAT, class P> struct Impl {
     using R = typename P::R;
+    static constexpr int SEAM_LV0 = Lat<LAT>::D - 1;   // seam levels from here on go to one workgroup
 
     static KP<R> &kp(lbfd_handle *h)
     {
@@ -2352,11 +2731,11 @@ template <int LAT, class P> struct Impl {
     {
         KP<R> &k = kp(h);
         LAUNCH(KC_FD, (k_fd<LAT, P>), h->grid, h->block, k);
-        for (int s = 0; s < h->sweeps_launch; ++s) {
-            // sweeps past the third usually find both systems converged and return at
-            // once: a narrower persistent grid makes that cheaper (the updates of a
-            // colour half-sweep do not depend on their order, so the result is the same)
-            const dim3 gs(s < 3 ? h->sor_blocks : std::min(h->sor_blocks, h->sor_narrow));
+        // the first sweeps by launches over the whole chip, the others (or, on small grids,
+        // all of them) by one persistent launch
+        const int lead = std::min(h->sweeps_launch, h->sor_lead);
+        for (int s = 0; s < lead; ++s) {
+            const dim3 gs(h->sor_blocks);
             if (h->seam_levels == 0) {
                 LAUNCH(KC_SOR, (k_sor<LAT, P, false>), gs, dim3(256), k, 0, s);
                 LAUNCH(KC_SOR, (k_sor<LAT, P, false>), gs, dim3(256), k, 1, s);
@@ -2364,10 +2743,20 @@ template <int LAT, class P> struct Impl {
             }
             LAUNCH(KC_SOR, (k_sor<LAT, P, true>), gs, dim3(256), k, 0, s);
             LAUNCH(KC_SOR, (k_sor<LAT, P, true>), gs, dim3(256), k, 1, s);
-            for (int lv = 1; lv <= h->seam_levels; ++lv) {
-                LAUNCH(KC_SOR, (k_sor_seam<LAT, P>), dim3(h->seam_tiles), dim3(256), k, lv, 0, s);
-                LAUNCH(KC_SOR, (k_sor_seam<LAT, P>), dim3(h->seam_tiles), dim3(256), k, lv, 1, s);
-            }
+            for (int c = 0; c < 2 && SEAM_LV0 > 1; ++c)
+                LAUNCH(KC_SOR, (k_sor_seam<LAT, P>), dim3(h->seam_tiles), dim3(256), k, 1, c, s);
+            if (h->seam_levels >= SEAM_LV0) LAUNCH(KC_SOR, (k_sor_seam<LAT, P>), dim3(1), dim3(256), k, -1, 0, s);
+        }
+        if (lead < h->sweeps_launch) {
+            const dim3 gr(h->rest_near ? 8 * h->rest_wgs : h->rest_wgs);
+            const int near = (int)h->rest_near;
+#define LAUNCH_REST(SEAM, ROWS) \
+    LAUNCH(KC_SOR, (k_sor_rest<LAT, P, SEAM, ROWS>), gr, dim3(REST_T), k, lead, h->sweeps_launch, near)
+            if (lead == 0 && h->seam_levels == 0) LAUNCH_REST(false, true);
+            else if (lead == 0) LAUNCH_REST(true, true);
+            else if (h->seam_levels == 0) LAUNCH_REST(false, false);
+            else LAUNCH_REST(true, false);
+#undef LAUNCH_REST
         }
         // the final reduction of the total also records the solve's sweeps and clears its slots
         totals(h, 1 - k.lev, 1 - k.pc, 1.0, 1, 1, h->sweeps_launch);
@@ -2500,30 +2889,30 @@ template <int LAT, class P> struct Impl {
             const bool fd = h->p.fd_enable != 0;
             if (fd) {
                 LAUNCH(KC_FD, (kb_fd<LAT, P>), b->grid_node, blk, tab, b->prefix_node, n, sa);
-                const dim3 g_late((unsigned)std::min((int)b->grid_sor.x, h->sor_narrow));
-                for (int s = 0; s < h->sweeps_launch; ++s) {
+                const int lead = std::min(h->sweeps_launch, b->sor_lead);
+                for (int s = 0; s < lead; ++s) {
                     for (int c = 0; c < 2; ++c) {
-                        if (s >= 3) {
-                            LAUNCH(KC_SOR, (kb_sor_live<LAT, P>), dim3(n), dim3(64), tab, c, s);
-                            if (b->seam_levels == 0)
-                                LAUNCH(KC_SOR, (kb_sor_late<LAT, P, false>), g_late, dim3(256), tab, b->prefix_sor, n, sa,
-                                       c, s);
-                            else
-                                LAUNCH(KC_SOR, (kb_sor_late<LAT, P, true>), g_late, dim3(256), tab, b->prefix_sor, n, sa,
-                                       c, s);
-                        } else if (b->seam_levels == 0) {
+                        if (b->seam_levels == 0)
                             LAUNCH(KC_SOR, (kb_sor<LAT, P, false>), b->grid_sor, dim3(256), tab, b->prefix_sor, n, sa, c, s);
-                        } else {
+                        else
                             LAUNCH(KC_SOR, (kb_sor<LAT, P, true>), b->grid_sor, dim3(256), tab, b->prefix_sor, n, sa, c, s);
-                        }
                     }
                     if (b->seam_levels == 0) continue;
-                    for (int lv = 1; lv <= b->seam_levels; ++lv) {
-                        LAUNCH(KC_SOR, (kb_sor_seam<LAT, P>), b->grid_seam, dim3(256), tab, b->prefix_seam, n, sa, lv,
-                               0, s);
-                        LAUNCH(KC_SOR, (kb_sor_seam<LAT, P>), b->grid_seam, dim3(256), tab, b->prefix_seam, n, sa, lv,
-                               1, s);
-                    }
+                    for (int c = 0; c < 2 && SEAM_LV0 > 1; ++c)
+                        LAUNCH(KC_SOR, (kb_sor_seam<LAT, P>), b->grid_seam, dim3(256), tab, b->prefix_seam, n, sa, 1, c, s);
+                    if (b->seam_levels >= SEAM_LV0)
+                        LAUNCH(KC_SOR, (kb_sor_seam<LAT, P>), dim3(n), dim3(256), tab, (const int *)nullptr, n, sa, -1, 0, s);
+                }
+                if (lead < h->sweeps_launch) {
+                    const dim3 gr((unsigned)(8 * ((b->rest_groups + 7) / 8) * b->rest_wgs));
+#define LAUNCH_REST(SEAM, ROWS)                                                                          \
+    LAUNCH(KC_SOR, (kb_sor_rest<LAT, P, SEAM, ROWS>), gr, dim3(REST_T), tab, n, sa, lead, h->sweeps_launch, \
+           b->rest_groups, b->rest_wgs)
+                    if (lead == 0 && b->seam_levels == 0) LAUNCH_REST(false, true);
+                    else if (lead == 0) LAUNCH_REST(true, true);
+                    else if (b->seam_levels == 0) LAUNCH_REST(false, false);
+                    else LAUNCH_REST(true, false);
+#undef LAUNCH_REST
                 }
                 LAUNCH(KC_TOTAL, (kb_total_part<LAT, P>), b->grid_total, dim3(256), tab, b->prefix_total, n,
                        1 - sa.lev, 1 - sa.pc, 1.0, 1);
@@ -2774,10 +3163,42 @@ template <int LAT, class P> struct Impl {
     }
 };
 
+// Shape of the implicit solve: sweeps by half-sweep launches (lead), then the persistent
+// launch of `wgs` workgroups, on one XCD (near) or on all of them.
+//
+// Launches that find both systems converged cost 2 to 3 us each, and a solve that needs
+// two sweeps of a budget of sixty had 116 of them: they were 0.32 of the 0.38 ms of a step
+// of the 128 x 128 drop (FP64) and 0.26 of 1.3 ms on the 128 x 128 x 384 column. The
+// persistent launch replaces them. Where each of its workgroups has one tile of a colour
+// (up to one workgroup per compute unit), it also takes the sweeps that do work, with the
+// rows in registers: a phase is 2.5 us on one XCD and 4 us on all of them against a launch of
+// 4.5 us (four sweeps of the 128 x 128 drop: 29 us near, 34 us on all XCDs, 43 us as three
+// sweeps of launches and the rest; 512 x 256 FP32: 27 against 33 us). With more tiles than
+// that a launch over the whole chip is faster than a phase (105^3 FP64: 18 against some
+// 30 us; 96^3 FP32: three sweeps 72 against 87 us), so the first three sweeps, as many as
+// most steps need, are launches.
+struct RestShape {
+    int lead, wgs;
+    bool near;
+};
+constexpr int REST_LEAD = 3;
+constexpr int REST_NEAR = 32;   // workgroups on one XCD: one per compute unit
+long long rest_tiles(const lbfd_params *p)
+{
+    return ((long long)((p->nx + 1) / 2) * p->ny * p->nz + REST_T - 1) / REST_T;
+}
+RestShape rest_shape(const lbfd_params *p, int narrow, int cus)
+{
+    const long long t = rest_tiles(p);
+    const int most = std::min(cus, SYNC_MAX);
+    if (t <= most) return RestShape{0, (int)t, t <= REST_NEAR};
+    return RestShape{REST_LEAD, std::min(narrow, most), false};
+}
+
 // Launch shape of a handle: rows of 64 x per workgroup of the step's node kernels,
-// and the SOR's persistent grid (workgroups of 256 per compute unit, capped at one
-// per tile of a colour; a multiple of 8 keeps the XCD-aware tile order) and the
-// grid of sweeps past the third. The results do not depend on it.
+// the grid of the SOR half-sweep launches (workgroups of 256 per compute unit, capped
+// at one per tile of a colour; a multiple of 8 keeps the XCD-aware tile order) and the
+// persistent launch behind them. The results do not depend on it.
 void apply_shape(lbfd_handle *h, int rows, int wg_per_cu, int narrow)
 {
     const lbfd_params *p = &h->p;
@@ -2790,6 +3211,23 @@ void apply_shape(lbfd_handle *h, int rows, int wg_per_cu, int narrow)
     h->sor_wg_per_cu = wg_per_cu;
     h->sor_blocks = (int)(need < cap ? need : cap);
     h->sor_narrow = narrow;
+    const RestShape r = rest_shape(p, narrow, h->cus);
+    h->sor_lead = r.lead;
+    h->rest_wgs = r.wgs;
+    h->rest_near = r.near;
+}
+
+// The same for a batch, by its largest instance: a group on one XCD per instance. Instances
+// of up to one tile per workgroup are solved by it from the first sweep on (8 instances of
+// up to 64 x 192 nodes: 18 us against 37 us of launches); larger ones by launches over all
+// instances first (64 columns of 1e5 nodes: 0.37 ms against 0.44).
+void batch_rest_shape(lbfd_batch *b)
+{
+    long long t = 1;
+    for (const lbfd_handle *h : b->inst) t = std::max(t, rest_tiles(&h->p));
+    b->sor_lead = t <= REST_NEAR ? 0 : REST_LEAD;
+    b->rest_wgs = (int)std::min<long long>(t, REST_NEAR);
+    b->rest_groups = std::min(b->n, 256);
 }
 
 struct Dispatch {
@@ -2939,6 +3377,11 @@ int lbfd_create(const lbfd_params *p, void *d_workspace, size_t bytes, void *str
     fill_kp(h->kd, p, h->ws, Lo);
     fill_kp(h->kf, p, h->ws, Lo);
     h->obs_out = (double *)(h->ws + Lo.obs);
+    hipLaunchKernelGGL(k_sync_clear, dim3(1), dim3(256), 0, h->stream, h->kd.fld.sync);
+    if (hipGetLastError() != hipSuccess) {
+        delete h;
+        return LBFD_EHIP;
+    }
     *out = h;
     return LBFD_OK;
 }
@@ -3185,7 +3628,7 @@ int lbfd_batch_create(const lbfd_params *p, int32_t n, void *d_workspace, size_t
         }
         b->inst.push_back(h);
         pn[i + 1] = pn[i] + (int)h->nblocks;
-        ps[i + 1] = ps[i] + sor_tiles_of(p[i].nx, p[i].ny, p[i].nz);
+        ps[i + 1] = ps[i] + (sor_tiles_of(p[i].nx, p[i].ny, p[i].nz) + SORB_TILES - 1) / SORB_TILES;
         pt[i + 1] = pt[i] + h->tblocks;
         pm[i + 1] = pm[i] + h->seam_tiles;
         if (h->seam_levels > b->seam_levels) b->seam_levels = h->seam_levels;
@@ -3195,6 +3638,7 @@ int lbfd_batch_create(const lbfd_params *p, int32_t n, void *d_workspace, size_t
     b->prefix_sor = b->prefix_node + (n + 1);
     b->prefix_total = b->prefix_sor + (n + 1);
     b->prefix_seam = b->prefix_total + (n + 1);
+    batch_rest_shape(b);
     b->grid_node = dim3((unsigned)pn[n]);
     b->grid_sor = dim3((unsigned)ps[n]);
     b->grid_total = dim3((unsigned)pt[n]);

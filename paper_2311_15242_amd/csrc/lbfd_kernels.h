@@ -172,8 +172,6 @@ struct DevScalars {
     uint32_t tick;                // geometry launches since the state was set (one per step):
                                   // the time input of the stochastic rounding
     uint32_t sg_bad;              // nodes where a surrogate candidate changed psi or phi implausibly
-    uint32_t sor_live;            // batched solve, sweeps past the third: systems of this instance
-                                  // not yet converged before the coming half-sweep (bit 0 psi, bit 1 phi)
     double Mref;                  // total of the state a surrogate candidate starts from
 };
 
@@ -201,6 +199,16 @@ struct alignas(16) DescDev {
     uint32_t c01, c2u0;
 };
 
+// Meeting place of the workgroups of the persistent solve (k_sor_rest). Zero before
+// every solve; each group of words that different workgroups write has lines of its own.
+constexpr int SYNC_MAX = 256;            // most workgroups of one persistent solve
+constexpr uint32_t SYNC_CLOSED = 0x80000000u;
+struct alignas(128) SorSync {
+    uint32_t tickets, pad0[31];          // workgroups enrolled; SYNC_CLOSED: no more are taken
+    uint32_t members, pad1[31];          // their number once enrolment is over (0 before)
+    uint32_t flag[2][SYNC_MAX];          // phase << 2 | open systems, per member, by phase parity
+};
+
 template <class R> struct Fields {
     void *f[2];
     R *mac[2];      // planes: 0 rhoR, 1 rhoB, 2 rhoN, 3.. j
@@ -218,6 +226,7 @@ template <class R> struct Fields {
     V2<R> *rhs2, *cs2, *cw2;   // implicit solve: (psi, phi) pairs of right-hand sides, iterates, node weights
     double *part;   // reduction partials
     unsigned long long *sorres;  // residual and |rhs| maxima per field, sweep and slot (bits of doubles)
+    SorSync *sync;  // workgroups of the persistent solve (zero between solves)
     DevScalars *sc;
 };
 
@@ -401,6 +410,39 @@ template <class T> __device__ __forceinline__ void st(T *base, uint32_t idx, con
     *(GT *)((LBFD_GLOBAL char *)base + idx * (uint32_t)sizeof(T)) = v;
 }
 
+// Element idx of an array that other workgroups of the same launch write or read
+// meanwhile: relaxed accesses of device scope, which the caches of one compute unit or
+// XCD never answer with an old value. A pair moves as one 8-byte (FP32) or two
+// 8-byte (FP64) accesses.
+template <class T> __device__ __forceinline__ T ld_dev(const T *p)
+{
+    return __hip_atomic_load((const LBFD_GLOBAL T *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class T> __device__ __forceinline__ void st_dev(T *p, T v)
+{
+    __hip_atomic_store((LBFD_GLOBAL T *)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class R> __device__ __forceinline__ V2<R> ld_dev(const V2<R> *base, uint32_t idx)
+{
+    const uint64_t *p = (const uint64_t *)((const char *)base + idx * (uint32_t)sizeof(V2<R>));
+    if constexpr (sizeof(R) == 4) {
+        const uint64_t u = ld_dev(p);
+        return V2<R>{__uint_as_float((uint32_t)u), __uint_as_float((uint32_t)(u >> 32))};
+    } else {
+        return V2<R>{__longlong_as_double((long long)ld_dev(p)), __longlong_as_double((long long)ld_dev(p + 1))};
+    }
+}
+template <class R> __device__ __forceinline__ void st_dev(V2<R> *base, uint32_t idx, const V2<R> &v)
+{
+    uint64_t *p = (uint64_t *)((char *)base + idx * (uint32_t)sizeof(V2<R>));
+    if constexpr (sizeof(R) == 4) {
+        st_dev(p, (uint64_t)__float_as_uint(v.x) | (uint64_t)__float_as_uint(v.y) << 32);
+    } else {
+        st_dev(p, (uint64_t)__double_as_longlong(v.x));
+        st_dev(p + 1, (uint64_t)__double_as_longlong(v.y));
+    }
+}
+
 // The same through a base that has one value in every lane (a plane of a
 // population array), pinned to scalar registers: otherwise the compiler may fold
 // the plane offset into per-lane 64-bit address arithmetic. The access goes
@@ -574,11 +616,39 @@ __device__ __forceinline__ double fast_rcp(double x) { return 1.0 / x; }
 
 // ------------------------------------------------------------------ wave reductions
 
+// Maximum over the wavefront, in every lane: within rows of 16 lanes, then across them, by
+// data-parallel moves (one VALU instruction a word, where a shuffle goes through the LDS
+// pipe), from lane 63. Every lane must be active.
+template <int CTRL> __device__ __forceinline__ float dpp_mov(float v)
+{
+    const int i = __float_as_int(v);
+    return __int_as_float(__builtin_amdgcn_update_dpp(i, i, CTRL, 0xf, 0xf, false));
+}
+template <int CTRL> __device__ __forceinline__ double dpp_mov(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = (int)(uint32_t)b, hi = (int)(uint32_t)((unsigned long long)b >> 32);
+    const uint32_t l = (uint32_t)__builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false);
+    const uint32_t h = (uint32_t)__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false);
+    return __longlong_as_double((long long)((unsigned long long)h << 32 | l));
+}
+__device__ __forceinline__ float lane63(float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63)); }
+__device__ __forceinline__ double lane63(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const uint32_t l = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, 63);
+    const uint32_t h = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((unsigned long long)b >> 32), 63);
+    return __longlong_as_double((long long)((unsigned long long)h << 32 | l));
+}
 template <class T> __device__ __forceinline__ T wave_max(T v)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
-    return v;
+    v = fmax(v, dpp_mov<0x111>(v));   // row_shr:1, 2, 4, 8
+    v = fmax(v, dpp_mov<0x112>(v));
+    v = fmax(v, dpp_mov<0x114>(v));
+    v = fmax(v, dpp_mov<0x118>(v));
+    v = fmax(v, dpp_mov<0x142>(v));   // row_bcast:15, 31
+    v = fmax(v, dpp_mov<0x143>(v));
+    return lane63(v);
 }
 
 __device__ __forceinline__ void atomic_max_nonneg(unsigned long long *addr, double v)
@@ -605,7 +675,7 @@ __device__ __forceinline__ void block_max_to_slots(R v0, R v1, unsigned long lon
     __shared__ double red[2][16];
     const int t = threadIdx.x + threadIdx.y * blockDim.x;
     const int lane = t & 63, wv = t >> 6, nw = (blockDim.x * blockDim.y) >> 6;
-    const double a = wave_max((double)v0), b = wave_max((double)v1);
+    const double a = (double)wave_max(v0), b = (double)wave_max(v1);
     if (lane == 0) { red[0][wv] = a; red[1][wv] = b; }
     __syncthreads();
     if (t == 0) {
@@ -621,15 +691,20 @@ __device__ __forceinline__ void block_max_to_slots(R v0, R v1, unsigned long lon
     __syncthreads();
 }
 
-// Zero the slots of the 2 nsw half-sweeps and of max |rhs| (threads of one block).
-__device__ __forceinline__ void sor_slots_clear(unsigned long long *base, int nsw)
+// Zero the slots of the half-sweeps of the first n0 (psi) and n1 (phi) sweeps and of max
+// |rhs|, and the meeting place of the persistent solve (threads of one block).
+__device__ __forceinline__ void sor_slots_clear(unsigned long long *base, SorSync *sync, int n0, int n1)
 {
     const int t = threadIdx.x + threadIdx.y * blockDim.x, nt = blockDim.x * blockDim.y;
-    const int per = (2 * nsw + 1) * RSLOTS;
-    for (int i = t; i < 2 * per; i += nt) {
-        const int fi = i / per, r = i % per, e = r / RSLOTS, slot = r % RSLOTS;
-        *res_slot(base, fi, e == 2 * nsw ? RMAX_IDX : e, slot) = 0ull;
+#pragma unroll
+    for (int fi = 0; fi < 2; ++fi) {
+        const int ne = 2 * (fi == 0 ? n0 : n1);
+        for (int i = t; i < (ne + 1) * RSLOTS; i += nt) {
+            const int e = i / RSLOTS;
+            *res_slot(base, fi, e == ne ? RMAX_IDX : e, i % RSLOTS) = 0ull;
+        }
     }
+    for (int i = t; i < (int)(sizeof(SorSync) / 4); i += nt) ((uint32_t *)sync)[i] = 0u;
 }
 
 }  // namespace lbfd
