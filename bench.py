@@ -827,7 +827,7 @@ def cpu_windows():
 
 
 KERNEL_CLASS_OF = {"k_collide<": "collide", "k_macro<": "macro", "k_geom<": "geom", "k_fd<": "fd",
-                   "k_sor<": "sor", "k_total_part<": "total", "k_force<": "force"}
+                   "k_sor<": "sor", "k_total<": "total", "k_force<": "force"}
 
 
 def kernel_class(name):

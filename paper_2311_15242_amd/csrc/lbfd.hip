@@ -39,15 +39,18 @@ namespace lbfd {
 constexpr int BX = 64, BY = 4;          // one wavefront spans 64 consecutive x
 static_assert(BX == 64, "node kernels hold y in scalar registers: a wavefront must be one row");
 constexpr int NRED = 19;                 // observable partial sums per block
-constexpr int TOTAL_BLOCKS = 1024;       // most workgroups of the total-surfactant sum
-constexpr int TOTAL_NODES = 4096;        // nodes per workgroup of that sum below the cap
+constexpr int TOTAL_T = 1024;            // threads of a workgroup of the total-surfactant sum
+constexpr int TOTAL_BLOCKS = 512;        // its most workgroups
 
 // Workgroups of the total-surfactant sum of an N-node grid. A function of N
 // alone, so the summation order (and the rounded total) of an instance is the
-// same whether it is stepped alone or in a batch.
-inline int total_blocks(long long N)
+// same whether it is stepped alone or in a batch. A node per thread on small
+// grids, where the sum is one chain of latencies (128^2: 8 us, 10 with four);
+// four on larger ones, where a batch has such a chain for every workgroup (64
+// columns of 1e5 nodes: 85 us with one, 53 with four).
+__host__ __device__ inline int total_blocks(long long N)
 {
-    const long long b = (N + TOTAL_NODES - 1) / TOTAL_NODES;
+    const long long per = N <= 32768 ? TOTAL_T : 4 * TOTAL_T, b = (N + per - 1) / per;
     return (int)(b < 1 ? 1 : b > TOTAL_BLOCKS ? TOTAL_BLOCKS : b);
 }
 
@@ -1756,51 +1759,51 @@ template <class R> __device__ __forceinline__ void sor_record(const KP<R> &k, in
 {
     DevScalars *sc = k.fld.sc;
     const int lane = threadIdx.x & 63;
-    // residual maxima of the sweeps, four sweeps' slots loaded before any is reduced
-    const auto res = [&](int fi, int e) { return e <= 2 * nsw ? bits_to_double(*res_slot(k.fld.sorres, fi, e, lane)) : 0.0; };
-    for (int fi = 0; fi < 2; ++fi) {
-        const double rm = wave_max(bits_to_double(*res_slot(k.fld.sorres, fi, RMAX_IDX, lane)));
-        const double lim = (double)k.tol * rm;
-        int K = nsw;
-        bool ok = false;
-        if (k.sor_exact) {
-            // whole residual after s sweeps = red residual at the start of sweep s
-            for (int s0 = 1; s0 < nsw && !ok; s0 += 4) {
-                double v[4];
+    const auto res = [&](int fi, int e) { return e < 2 * nsw ? bits_to_double(*res_slot(k.fld.sorres, fi, e, lane)) : 0.0; };
+    double rm[2], lim[2];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = res(fi, 2 * (s0 + i));
+    for (int fi = 0; fi < 2; ++fi) rm[fi] = bits_to_double(*res_slot(k.fld.sorres, fi, RMAX_IDX, lane));
+    int K[2] = {0, 0};   // 0: not found yet
+    // both systems, eight sweeps at a time, all their slots loaded before any is tested. Sweep s
+    // is the last one if the whole residual after it is within the tolerance: the red
+    // residual at the start of sweep s (sor_exact), or both residuals of sweep s - 1
+    const int end = k.sor_exact ? nsw - 1 : nsw;
+    for (int s0 = 1; s0 <= end && (K[0] == 0 || K[1] == 0); s0 += 8) {
+        double v[2][8];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int s = s0 + i;
-                    if (ok || s >= nsw) continue;
-                    if (wave_max(v[i]) <= lim) { K = s; ok = true; }
-                }
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int fi = 0; fi < 2; ++fi) {
+                const int s = s0 + i;
+                v[fi][i] = k.sor_exact ? res(fi, 2 * s) : fmax(res(fi, 2 * (s - 1)), res(fi, 2 * (s - 1) + 1));
             }
-        } else {
-            for (int s0 = 1; s0 <= nsw && !ok; s0 += 4) {
-                double v[4], w[4];
+        if (s0 == 1) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    v[i] = res(fi, 2 * (s0 + i - 1));
-                    w[i] = res(fi, 2 * (s0 + i - 1) + 1);
-                }
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int s = s0 + i;
-                    if (ok || s > nsw) continue;
-                    if (fmax(wave_max(v[i]), wave_max(w[i])) <= lim) { K = s; ok = true; }
-                }
+            for (int fi = 0; fi < 2; ++fi) {
+                rm[fi] = wave_max(rm[fi]);
+                lim[fi] = (double)k.tol * rm[fi];
             }
         }
-        if (lane == 0) {
-            sc->rmax[fi] = (unsigned long long)__double_as_longlong(rm);
-            sc->sweeps[fi] = K;
-            counts[fi] = K;
-            if (!ok && sc->status == 0) sc->status = LBFD_ESOR;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int fi = 0; fi < 2; ++fi)
+                if (K[fi] == 0 && s0 + i <= end && __ballot(!(v[fi][i] <= lim[fi])) == 0ull) K[fi] = s0 + i;
+    }
+    if (end < 1) {
+#pragma unroll
+        for (int fi = 0; fi < 2; ++fi) rm[fi] = wave_max(rm[fi]);
+    }
+    if (lane == 0) {
+#pragma unroll
+        for (int fi = 0; fi < 2; ++fi) {
+            sc->rmax[fi] = (unsigned long long)__double_as_longlong(rm[fi]);
+            sc->sweeps[fi] = counts[fi] = K[fi] ? K[fi] : nsw;
         }
+        if ((K[0] == 0 || K[1] == 0) && sc->status == 0) st_dev(&sc->status, (int32_t)LBFD_ESOR);
     }
 }
-// Clears the residual and |rhs| slots (set-up, before the first step).
+
 // An idle meeting place for the persistent solve (at creation).
 __global__ void k_sync_clear(SorSync *s)
 {
@@ -1968,18 +1971,45 @@ template <int NV> __device__ __forceinline__ void block_sum_store(double (&v)[NV
         for (int i = 0; i < NV; ++i) out[i] = sh[i][0];
 }
 
-// Per-block FP64 sums of G psi + X phi (the conserved integrand of eqs 20-21)
-// at `level`, psi/phi from buffer `buf` times `mult` (mult < 0: the device's
-// rescaling factor, which turns stored values into physical ones).
+// Total of G psi + X phi (the conserved integrand of eqs 20-21), FP64, at `level`, psi/phi from
+// buffer `buf` times `mult` (mult < 0: the device's rescaling factor, which turns stored
+// values into physical ones), and what follows from it (mode). One launch: every workgroup
+// leaves its sum, and the one that finds all the others' there adds them up, always in the
+// same order. After a solve (nsw > 0) workgroup 0 also records its sweeps and clears what it
+// left, beside the others' sums.
+//
+// Bound: HBM on large grids (4.5 TB/s at 6.3e6 nodes), latency on small ones, hence up to
+// TOTAL_BLOCKS workgroups and no second launch for the final sum (128^2 nodes: 17 us in two
+// launches, of 4096 nodes a workgroup).
+// Sum over the workgroup in thread 0, always in the same order. sh: one value per wavefront.
+__device__ __forceinline__ double block_sum(double v, double *sh)
+{
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    const int t = threadIdx.x, nw = blockDim.x >> 6;
+    __syncthreads();   // an earlier sum has been read
+    if ((t & 63) == 0) sh[t >> 6] = v;
+    __syncthreads();
+    v = 0.0;
+    if (t == 0)
+        for (int w = 0; w < nw; ++w) v += sh[w];
+    return v;
+}
 template <int LAT, class P>
-__device__ __forceinline__ void total_part_body(const KP<typename P::R> &k, int level, int buf, double mult, int blk,
-                                                int nblk, int from_split)
+__device__ __forceinline__ void total_body(const KP<typename P::R> &k, int level, int buf, double mult, int blk,
+                                           int nblk, int from_split, int mode, int nsw)
 {
     using R = typename P::R;
     const long long N = k.N;
-    if (mult < 0.0) mult = k.fld.sc->scale;
-    double v[1] = {0.0};
-    for (long long n = (long long)blk * blockDim.x + threadIdx.x; n < N; n += (long long)nblk * blockDim.x) {
+    const int t = threadIdx.x;
+    DevScalars *sc = k.fld.sc;
+    __shared__ double sh[TOTAL_T / 64];
+    __shared__ int counts[2];
+    __shared__ uint32_t last;
+    if (nsw > 0 && blk == 0 && t < 64) sor_record(k, nsw, counts);
+    if (mult < 0.0) mult = sc->scale;
+    double v = 0.0;
+    for (long long n = (long long)blk * TOTAL_T + t; n < N; n += (long long)nblk * TOTAL_T) {
         const uint32_t i = (uint32_t)n;
         double G = (double)(ld(k.fld.G[level], i) + k.fd_eps);
         double X = (double)((R(1) - ld(k.fld.mac[level] + 2 * N, i)) + k.fd_eps);
@@ -1998,78 +2028,61 @@ __device__ __forceinline__ void total_part_body(const KP<typename P::R> &k, int 
             vp = ld(k.fld.psi[buf], i);
             vf = ld(k.fld.phi[buf], i);
         }
-        v[0] += G * (mult * (double)vp) + X * (mult * (double)vf);
+        v += G * (mult * (double)vp) + X * (mult * (double)vf);
     }
-    block_sum_store<1>(v, k.fld.part + blk);
+    v = block_sum(v, sh);
+    if (t == 0) {
+        // the sum (and workgroup 0's status) has reached device scope before it is counted
+        st_dev((unsigned long long *)&k.fld.part[blk], (unsigned long long)__double_as_longlong(v));
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        last = __hip_atomic_fetch_add(&sc->total_done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)nblk - 1u;
+    }
+    __syncthreads();
+    // the residual slots the solve wrote, for the next one (a system is updated, and records,
+    // in at most one sweep past its count)
+    if (nsw > 0 && blk == 0)
+        sor_slots_clear(k.fld.sorres, k.fld.sync, min(counts[0] + 1, nsw), min(counts[1] + 1, nsw));
+    if (!last) return;
+    double a = 0.0;
+    for (int b = t; b < nblk; b += TOTAL_T) a += bits_to_double(ld_dev((const unsigned long long *)&k.fld.part[b]));
+    const double M = block_sum(a, sh);
+    if (t != 0) return;
+    sc->total_done = 0u;
+    if (mode == 0) {
+        sc->M0 = M;
+        sc->Mlast = M;
+        sc->drift_pre = 0.0;
+        sc->scale = 1.0;
+        sc->scale_prev = 1.0;
+    } else if (mode == 2) {
+        // probe: the relative change of the total that a candidate makes to the
+        // state it starts from (mode 3), at the same weights (nothing else changes)
+        sc->drift_pre = sc->Mref != 0.0 ? (M - sc->Mref) / sc->Mref : 0.0;
+    } else if (mode == 3) {
+        sc->Mref = M;
+    } else {
+        sc->scale_prev = sc->scale;
+        sc->Mlast = M;
+        sc->drift_pre = sc->M0 != 0.0 ? (M - sc->M0) / sc->M0 : 0.0;
+        sc->scale = (k.rescale && sc->M0 != 0.0 && M != 0.0) ? sc->M0 / M : 1.0;
+        if (!isfinite(M) && ld_dev(&sc->status) == 0) sc->status = LBFD_ENONFINITE;
+    }
 }
 template <int LAT, class P>
-__global__ __launch_bounds__(256) void k_total_part(KP<typename P::R> k, int level, int buf, double mult,
-                                                   int from_split)
+__global__ __launch_bounds__(TOTAL_T) void k_total(KP<typename P::R> k, int level, int buf, double mult, int from_split,
+                                              int mode, int nsw)
 {
-    total_part_body<LAT, P>(k, level, buf, mult, (int)blockIdx.x, (int)gridDim.x, from_split);
+    total_body<LAT, P>(k, level, buf, mult, (int)blockIdx.x, (int)gridDim.x, from_split, mode, nsw);
 }
-// batch: instance i owns workgroups prefix[i] .. prefix[i+1]-1
+// batch: instance i owns workgroups prefix[i] .. prefix[i+1]-1 (of one XCD, as in the solve
+// before: dealt over all of them, with a row of the grid per instance, it took 90 us)
 template <int LAT, class P>
-__global__ __launch_bounds__(256) void kb_total_part(const KP<typename P::R> *tab, const int *prefix, int ninst,
-                                                    int level, int buf, double mult, int from_split)
+__global__ __launch_bounds__(TOTAL_T) void kb_total(const KP<typename P::R> *tab, const int *prefix, int ninst, int level,
+                                                   int buf, double mult, int from_split, int mode, int nsw)
 {
     int inst, local;
     batch_tile(prefix, ninst, inst, local);
-    total_part_body<LAT, P>(tab[inst], level, buf, mult, local, prefix[inst + 1] - prefix[inst], from_split);
-}
-template <class R> __device__ __forceinline__ void total_final_body(const KP<R> &k, long long nblocks, int mode, int nsw)
-{
-    __shared__ double sh[256];
-    const int t = threadIdx.x;
-    if (nsw > 0) {
-        // after a solve: record its sweeps (first wavefront), then clear the residual slots
-        // it wrote for the next one (a system is updated, and records, in at most one
-        // sweep past its count; the total's partial sums read none of the slots)
-        __shared__ int counts[2];
-        if (t < 64) sor_record(k, nsw, counts);
-        __syncthreads();
-        sor_slots_clear(k.fld.sorres, k.fld.sync, min(counts[0] + 1, nsw), min(counts[1] + 1, nsw));
-    }
-    double a = 0.0;
-    for (long long b = t; b < nblocks; b += 256) a += k.fld.part[b];
-    sh[t] = a;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w) sh[t] += sh[t + w];
-        __syncthreads();
-    }
-    if (t == 0) {
-        DevScalars *sc = k.fld.sc;
-        double M = sh[0];
-        if (mode == 0) {
-            sc->M0 = M;
-            sc->Mlast = M;
-            sc->drift_pre = 0.0;
-            sc->scale = 1.0;
-            sc->scale_prev = 1.0;
-        } else if (mode == 2) {
-            // probe: the relative change of the total that a candidate makes to the
-            // state it starts from (mode 3), at the same weights (nothing else changes)
-            sc->drift_pre = sc->Mref != 0.0 ? (M - sc->Mref) / sc->Mref : 0.0;
-        } else if (mode == 3) {
-            sc->Mref = M;
-        } else {
-            sc->scale_prev = sc->scale;
-            sc->Mlast = M;
-            sc->drift_pre = sc->M0 != 0.0 ? (M - sc->M0) / sc->M0 : 0.0;
-            sc->scale = (k.rescale && sc->M0 != 0.0 && M != 0.0) ? sc->M0 / M : 1.0;
-            if (!isfinite(M) && sc->status == 0) sc->status = LBFD_ENONFINITE;
-        }
-    }
-}
-template <class R> __global__ void k_total_final(KP<R> k, long long nblocks, int mode, int nsw)
-{
-    total_final_body(k, nblocks, mode, nsw);
-}
-template <class R> __global__ void kb_total_final(const KP<R> *tab, const int *prefix, int mode, int nsw)
-{
-    const int i = blockIdx.x;
-    total_final_body(tab[i], (long long)(prefix[i + 1] - prefix[i]), mode, nsw);
+    total_body<LAT, P>(tab[inst], level, buf, mult, local, prefix[inst + 1] - prefix[inst], from_split, mode, nsw);
 }
 
 // Observables, pass 0: sums and extrema; pass 1: central second moments.
@@ -2621,8 +2634,8 @@ template <int LAT, class P> struct Impl {
                        int solve_sweeps = 0)
     {
         KP<R> &k = kp(h);
-        LAUNCH(KC_TOTAL, (k_total_part<LAT, P>), dim3(h->tblocks), dim3(256), k, level, buf, mult, from_split);
-        LAUNCH(KC_TOTAL, (k_total_final<R>), dim3(1), dim3(256), k, (long long)h->tblocks, mode, solve_sweeps);
+        LAUNCH(KC_TOTAL, (k_total<LAT, P>), dim3(h->tblocks), dim3(TOTAL_T), k, level, buf, mult, from_split, mode,
+               solve_sweeps);
     }
 
     static void derived(lbfd_handle *h)
@@ -2758,7 +2771,7 @@ template <int LAT, class P> struct Impl {
             else LAUNCH_REST(true, false);
 #undef LAUNCH_REST
         }
-        // the final reduction of the total also records the solve's sweeps and clears its slots
+        // the total also records the solve's sweeps and clears its slots
         totals(h, 1 - k.lev, 1 - k.pc, 1.0, 1, 1, h->sweeps_launch);
         h->pc = 1 - h->pc;
         h->fd_hist += 1;
@@ -2914,9 +2927,8 @@ template <int LAT, class P> struct Impl {
                     else LAUNCH_REST(true, false);
 #undef LAUNCH_REST
                 }
-                LAUNCH(KC_TOTAL, (kb_total_part<LAT, P>), b->grid_total, dim3(256), tab, b->prefix_total, n,
-                       1 - sa.lev, 1 - sa.pc, 1.0, 1);
-                LAUNCH(KC_TOTAL, (kb_total_final<R>), dim3(n), dim3(256), tab, b->prefix_total, 1, h->sweeps_launch);
+                LAUNCH(KC_TOTAL, (kb_total<LAT, P>), b->grid_total, dim3(TOTAL_T), tab, b->prefix_total, n, 1 - sa.lev,
+                       1 - sa.pc, 1.0, 1, 1, h->sweeps_launch);
             }
             for (lbfd_handle *x : b->inst) {
                 if (fd) {

@@ -155,8 +155,12 @@ static_assert(rows_have_parity<0>() && rows_have_parity<1>(), "moment rows witho
 
 constexpr int QMAX = 19;
 constexpr int MAX_SWEEPS = 256;
-constexpr int RSLOTS = 64;    // residual maxima of a sweep are spread over this many cache lines
-constexpr int RSTRIDE = 16;   // 128 bytes between slots
+// Residual maxima of a sweep are spread over RSLOTS slots of RSTRIDE values: eight to a
+// cache line, enough lines for the atomic maxima of a launch not to queue, few enough for
+// the test at the start of every workgroup to read them quickly (a line each: 64 columns
+// of 1e5 nodes 45 us a half-sweep instead of 40, 105^3 FP64 18 instead of 15).
+constexpr int RSLOTS = 64;
+constexpr int RSTRIDE = 2;
 
 // Device-resident scalars: the rescaling factor, the rescaling target, and the
 // bookkeeping of the implicit solve and of error detection.
@@ -171,6 +175,7 @@ struct DevScalars {
     int32_t status;               // sticky lbfd_status of device-detected errors
     uint32_t tick;                // geometry launches since the state was set (one per step):
                                   // the time input of the stochastic rounding
+    uint32_t total_done;          // workgroups of a running total that have left their sum (0 between launches)
     uint32_t sg_bad;              // nodes where a surrogate candidate changed psi or phi implausibly
     double Mref;                  // total of the state a surrogate candidate starts from
 };
