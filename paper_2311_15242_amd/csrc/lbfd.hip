@@ -3721,6 +3721,7 @@ struct lbfd_sg {
     sg::Net net;
     float *gflat;            // gradient in parameter order [n_params]
     double *loss;            // FP64 loss accumulator
+    long long grad_words;    // 16-byte words from gw[0] to the end of the loss: zero before a backward pass
     uint16_t *act[3];        // outputs of layers 1-3, BF16 [nodes][32]
     uint16_t *dy[2];         // gradients of layer outputs, BF16 [nodes][32]
     float *out;              // network output, FP32 [nodes][NOUT]
@@ -3728,8 +3729,7 @@ struct lbfd_sg {
     int *org;                // tile origins [3 max_batch]
     long long cap_act, cap_out, cap_feat;
     long long t;             // Adam steps taken
-    bool wide = true;        // z-marching kernel on wide grids
-    int cus = 256;           // compute units of the device (persistent grid of that kernel)
+    int cus = 256;           // compute units of the device (persistent grids of the layers)
 };
 
 static long long cube(long long e) { return e * e * e; }
@@ -3742,7 +3742,7 @@ static long long layer_nodes(int l, long long B, long long d, long long h, long 
 
 struct SgLayout {
     size_t master, m, v, gflat, gw[sg::NL], gb[sg::NL], wb[sg::NL], wt[sg::NL], bias[sg::NL];
-    size_t loss, act[3], dy[2], out, feat, org, total;
+    size_t loss, grad_end, net_end, act[3], dy[2], out, feat, org, total;
     long long cap_act, cap_out, cap_feat;
 };
 
@@ -3771,14 +3771,19 @@ static int sg_layout(const lbfd_sg_params *p, SgLayout *L)
     L->m = take(4 * np);
     L->v = take(4 * np);
     L->gflat = take(4 * np);
+    // what a backward pass starts from zero, in one piece
     for (int l = 0; l < sg::NL; ++l) {
         L->gw[l] = take(4 * 27 * sg::CIN_PAD[l] * sg::CO);
         L->gb[l] = take(4 * sg::CO);
+    }
+    L->loss = take(8);
+    L->grad_end = o;
+    for (int l = 0; l < sg::NL; ++l) {
         L->wb[l] = take(2 * 27 * sg::CIN_PAD[l] * sg::CO);
         L->wt[l] = take(2 * 27 * sg::CIN_PAD[l] * sg::CO);
         L->bias[l] = take(4 * sg::CO);
     }
-    L->loss = take(8);
+    L->net_end = o;
     for (int i = 0; i < 3; ++i) L->act[i] = take((size_t)ca * sg::CO * 2);
     for (int i = 0; i < 2; ++i) L->dy[i] = take((size_t)ca * sg::CO * 2);
     L->out = take((size_t)co * sg::NOUT * 4);
@@ -3828,6 +3833,7 @@ int lbfd_sg_create(const lbfd_sg_params *p, void *d_workspace, size_t bytes, voi
     }
     s->gflat = (float *)(ws + L.gflat);
     s->loss = (double *)(ws + L.loss);
+    s->grad_words = (long long)(L.grad_end - L.gw[0]) / 16;
     for (int i = 0; i < 3; ++i) s->act[i] = (uint16_t *)(ws + L.act[i]);
     for (int i = 0; i < 2; ++i) s->dy[i] = (uint16_t *)(ws + L.dy[i]);
     s->out = (float *)(ws + L.out);
@@ -3844,7 +3850,7 @@ int lbfd_sg_create(const lbfd_sg_params *p, void *d_workspace, size_t bytes, voi
             s->cus = n;
     }
     // weights, moments and the padded layouts start at zero
-    if (hipMemsetAsync(ws, 0, L.loss, s->stream) != hipSuccess || hipStreamSynchronize(s->stream) != hipSuccess) {
+    if (hipMemsetAsync(ws, 0, L.net_end, s->stream) != hipSuccess || hipStreamSynchronize(s->stream) != hipSuccess) {
         delete s;
         return LBFD_EHIP;
     }
@@ -3898,6 +3904,45 @@ static unsigned blocks_for(long long n, long long per) { return (unsigned)((n + 
 // Output planes per column of the z-marching forward kernel.
 constexpr int SG_ZC = 32;
 
+extern "C++" {
+// k_conv_rows over an output grid (the source grid is 2 smaller or larger along every axis).
+template <int CIN, int KIND>
+static void sg_conv_rows(const lbfd_sg *s, hipStream_t st, const uint16_t *in, const uint16_t *wb, const float *bias,
+                         const uint16_t *mask, void *out, int B, int Do, int Ho, int Wo)
+{
+    const int g = KIND == sg::DGRAD ? -2 : 2;
+    const int ry = sg::rows_per_unit(B, Do, Ho, Wo, s->cus), nyb = (Ho + ry - 1) / ry;
+    const long long units = (long long)B * Do * nyb;
+    const long long grid = std::min<long long>((units + 7) / 8 * 8, std::max(8, s->cus / 8 * 8));
+    hipLaunchKernelGGL((sg::k_conv_rows<CIN, KIND>), dim3((unsigned)grid), dim3(256), 0, st, in, wb, bias, mask, out,
+                       Do + g, Ho + g, Wo + g, Do, Ho, Wo, ry, nyb, (int)units);
+}
+
+// k_conv_fwd_zm over an input grid: columns of 30 x 8 output nodes over SG_ZC planes.
+template <int CIN, bool RELU, bool OUTF32>
+static void sg_conv_zm(const lbfd_sg *s, hipStream_t st, const uint16_t *in, const uint16_t *wb, const float *bias,
+                       void *out, int B, int Di, int Hi, int Wi)
+{
+    const int nbx = (Wi - 2 + sg::ZX - 1) / sg::ZX, nby = (Hi - 2 + sg::ZY - 1) / sg::ZY,
+              nbz = (Di - 2 + SG_ZC - 1) / SG_ZC;
+    const long long ncol = (long long)nbx * nby * nbz * B;
+    const long long most = std::max(8, s->cus * sg::zm_per_cu<CIN>() / 8 * 8);
+    hipLaunchKernelGGL((sg::k_conv_fwd_zm<CIN, RELU, OUTF32>), dim3((unsigned)std::min((ncol + 7) / 8 * 8, most)),
+                       dim3(256), 0, st, in, wb, bias, out, Di, Hi, Wi, nbx, nby, nbz, SG_ZC, ncol);
+}
+
+// Weight and bias gradients of layer l from its input x and its output gradient, on B grids of
+// Di^3 input nodes.
+template <int CIN>
+static void sg_wgrad(const lbfd_sg *s, hipStream_t st, const uint16_t *x, const uint16_t *dy, int l, int B, int Di)
+{
+    const int Do = Di - 2, ry = sg::rows_per_wgrad_unit(B, Do, Do, Do, s->cus), nyb = (Do + ry - 1) / ry;
+    const int units = B * Do * nyb, grid = std::min((units + 7) / 8 * 8, std::max(8, s->cus / 8 * 8));
+    hipLaunchKernelGGL((sg::k_conv_wgrad<CIN>), dim3((unsigned)grid), dim3(sg::WG_T), 0, st, x, dy, s->net.gw[l],
+                       s->net.gb[l], Di, Di, Di, ry, nyb, units);
+}
+}  // extern "C++"
+
 // Forward pass over B grids of d x h x w input nodes on stream st; the layer
 // outputs stay in s->act for a backward pass.
 static int sg_forward_on(lbfd_sg *s, hipStream_t st, const uint16_t *in, int B, int d, int h, int w, float *out)
@@ -3905,42 +3950,24 @@ static int sg_forward_on(lbfd_sg *s, hipStream_t st, const uint16_t *in, int B, 
     if (!s || !in || !out || B < 1 || d < 9 || h < 9 || w < 9) return LBFD_EINVAL;
     const long long M1 = layer_nodes(1, B, d, h, w), M4 = layer_nodes(4, B, d, h, w);
     if (M1 > s->cap_act || M4 > s->cap_out) return LBFD_EINVAL;
-    const void *x = in;
+    const uint16_t *x = in;
+    const sg::Net &n = s->net;
     for (int l = 0; l < sg::NL; ++l) {
         const int Di = d - 2 * l, Hi = h - 2 * l, Wi = w - 2 * l;
-        const long long M = layer_nodes(l + 1, B, d, h, w);
-        if (Wi - 2 >= 2 * sg::ZX && s->wide) {
-            // wide grids: columns of 30 x 4 output nodes over SG_ZC planes, one persistent
-            // workgroup per compute unit (the kernel's LDS and registers allow one)
-            const int nbx = (Wi - 2 + sg::ZX - 1) / sg::ZX, nby = (Hi - 2 + sg::ZY - 1) / sg::ZY,
-                      nbz = (Di - 2 + SG_ZC - 1) / SG_ZC;
-            const long long ncol = (long long)nbx * nby * nbz * B;
-            const dim3 grid((unsigned)std::min<long long>(ncol, s->cus));
-            if (l == 0)
-                hipLaunchKernelGGL((sg::k_conv_fwd_zm<16, true, false>), grid, dim3(256), 0, st, (const uint16_t *)x,
-                                   s->net.wb[0], s->net.bias[0], (void *)s->act[0], Di, Hi, Wi, nbx, nby, nbz, SG_ZC,
-                                   ncol);
-            else if (l < 3)
-                hipLaunchKernelGGL((sg::k_conv_fwd_zm<32, true, false>), grid, dim3(256), 0, st, (const uint16_t *)x,
-                                   s->net.wb[l], s->net.bias[l], (void *)s->act[l], Di, Hi, Wi, nbx, nby, nbz, SG_ZC,
-                                   ncol);
-            else
-                hipLaunchKernelGGL((sg::k_conv_fwd_zm<32, false, true>), grid, dim3(256), 0, st, (const uint16_t *)x,
-                                   s->net.wb[3], s->net.bias[3], (void *)out, Di, Hi, Wi, nbx, nby, nbz, SG_ZC, ncol);
-            if (l < 3) x = s->act[l];
-            continue;
+        void *y = l < 3 ? (void *)s->act[l] : (void *)out;
+        // from two full tiles of 30 along x on the marching kernel's partial rows cost less
+        // than staging three planes for every output plane
+        if (Wi - 2 >= 2 * sg::ZX) {
+            if (l == 0) sg_conv_zm<16, true, false>(s, st, x, n.wb[l], n.bias[l], y, B, Di, Hi, Wi);
+            else if (l < 3) sg_conv_zm<32, true, false>(s, st, x, n.wb[l], n.bias[l], y, B, Di, Hi, Wi);
+            else sg_conv_zm<32, false, true>(s, st, x, n.wb[l], n.bias[l], y, B, Di, Hi, Wi);
+        } else {
+            const int Do = Di - 2, Ho = Hi - 2, Wo = Wi - 2;
+            if (l == 0) sg_conv_rows<16, sg::FWD>(s, st, x, n.wb[l], n.bias[l], nullptr, y, B, Do, Ho, Wo);
+            else if (l < 3) sg_conv_rows<32, sg::FWD>(s, st, x, n.wb[l], n.bias[l], nullptr, y, B, Do, Ho, Wo);
+            else sg_conv_rows<32, sg::LAST>(s, st, x, n.wb[l], n.bias[l], nullptr, y, B, Do, Ho, Wo);
         }
-        const dim3 grid(blocks_for(M, sg::FWD_NODES));
-        if (l == 0)
-            hipLaunchKernelGGL((sg::k_conv_fwd<16, true, false>), grid, dim3(256), 0, st, (const uint16_t *)x,
-                               s->net.wb[0], s->net.bias[0], (void *)s->act[0], Di, Hi, Wi, M);
-        else if (l < 3)
-            hipLaunchKernelGGL((sg::k_conv_fwd<32, true, false>), grid, dim3(256), 0, st, (const uint16_t *)x,
-                               s->net.wb[l], s->net.bias[l], (void *)s->act[l], Di, Hi, Wi, M);
-        else
-            hipLaunchKernelGGL((sg::k_conv_fwd<32, false, true>), grid, dim3(256), 0, st, (const uint16_t *)x,
-                               s->net.wb[3], s->net.bias[3], (void *)out, Di, Hi, Wi, M);
-        if (l < 3) x = s->act[l];
+        x = s->act[l < 3 ? l : 2];
     }
     return hipGetLastError() == hipSuccess ? LBFD_OK : LBFD_EHIP;
 }
@@ -3957,12 +3984,8 @@ static int sg_backward(lbfd_sg *s, const uint16_t *in, const float *tgt, int B)
     const int E = s->p.tile + 8;
     int rc = sg_forward_on(s, st, in, B, E, E, E, s->out);
     if (rc != LBFD_OK) return rc;
-    for (int l = 0; l < sg::NL; ++l) {
-        if (hipMemsetAsync(s->net.gw[l], 0, sizeof(float) * 27 * sg::CIN_PAD[l] * sg::CO, st) != hipSuccess ||
-            hipMemsetAsync(s->net.gb[l], 0, sizeof(float) * sg::CO, st) != hipSuccess)
-            return LBFD_EHIP;
-    }
-    if (hipMemsetAsync(s->loss, 0, sizeof(double), st) != hipSuccess) return LBFD_EHIP;
+    hipLaunchKernelGGL(sg::k_zero, dim3(blocks_for(s->grad_words, 256)), dim3(256), 0, st, (sg::u32x4 *)s->net.gw[0],
+                       s->grad_words);
     const long long M4 = layer_nodes(4, B, E, E, E);
     const long long T = s->p.tile;
     const float scale = (float)(2.0 / (2.0 * (double)B * (double)cube(T - 2)));
@@ -3971,20 +3994,12 @@ static int sg_backward(lbfd_sg *s, const uint16_t *in, const float *tgt, int B)
     int cur = 0;   // s->dy[cur]: gradient at the output of layer l + 1
     for (int l = sg::NL - 1; l >= 0; --l) {
         const int Di = E - 2 * l;
-        const long long M = layer_nodes(l + 1, B, E, E, E);
         const uint16_t *x = l == 0 ? in : s->act[l - 1];
-        const long long S = std::min<long long>(256, std::max<long long>(1, (M + 4095) / 4096));
-        const long long per = ((M + S - 1) / S + 255) / 256 * 256;
-        if (l == 0)
-            hipLaunchKernelGGL((sg::k_conv_wgrad<16>), dim3(27, (unsigned)S), dim3(256), 0, st, x, s->dy[cur],
-                               s->net.gw[l], s->net.gb[l], Di, Di, Di, M, per);
-        else
-            hipLaunchKernelGGL((sg::k_conv_wgrad<32>), dim3(27, (unsigned)S), dim3(256), 0, st, x, s->dy[cur],
-                               s->net.gw[l], s->net.gb[l], Di, Di, Di, M, per);
+        if (l == 0) sg_wgrad<16>(s, st, x, s->dy[cur], l, B, Di);
+        else sg_wgrad<32>(s, st, x, s->dy[cur], l, B, Di);
         if (l > 0) {
-            const long long Mi = layer_nodes(l, B, E, E, E);
-            hipLaunchKernelGGL(sg::k_conv_dgrad, dim3(blocks_for(Mi, 256)), dim3(256), 0, st, s->dy[cur],
-                               s->net.wt[l], s->act[l - 1], s->dy[1 - cur], Di, Di, Di, Mi);
+            sg_conv_rows<sg::CO, sg::DGRAD>(s, st, s->dy[cur], s->net.wt[l], nullptr, s->act[l - 1], s->dy[1 - cur], B, Di,
+                                            Di, Di);
             cur = 1 - cur;
         }
     }

@@ -4,18 +4,18 @@
 // surrogate; the network and its training are defined in the public header.
 //
 // Every layer is an implicit GEMM. Forward: rows = output nodes, columns = the 32
-// (padded) output channels, reduction over 27 taps x input channels; on tiles one
-// wavefront computes several 32 x 32 tiles with the layer's weights in LDS, on wide
-// grids the weights stay in registers and the input marches through LDS by planes. Input gradient: rows =
-// input nodes, columns = input channels, reduction over taps x output channels
-// (the transposed weights). Weight gradient: one 32 x 32 tile (input x output
-// channels) per tap, reduction over nodes in 256-node chunks staged in LDS
-// transposed so every operand fragment is a 16-byte LDS read; partial tiles meet
-// in FP32 atomics (the bias gradient rides along in the blocks of one tap).
+// (padded) output channels, reduction over 27 taps x input channels, weights in
+// registers; on wide grids the input marches through LDS by planes (k_conv_fwd_zm), on
+// narrower ones rows of output nodes share three staged planes (k_conv_rows).
+// Input gradient: rows = input nodes, columns = input channels, reduction over taps x
+// output channels (the transposed weights), by k_conv_rows too. Weight gradient: one
+// 32 x 32 tile (input x output channels) per tap, reduction over nodes staged in LDS
+// and read transposed; partial sums meet in FP32 atomics (k_conv_wgrad).
 #pragma once
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace lbfd {
 namespace sg {
@@ -25,6 +25,7 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint16_t u16;
 
 constexpr int NL = 4;                                  // layers
@@ -58,105 +59,72 @@ __device__ __forceinline__ bf16x8 frag_zero() { return __builtin_bit_cast(bf16x8
 // column is the lane index mod 32).
 __device__ __forceinline__ int acc_row(int r, int kg) { return 8 * (r >> 2) + 4 * kg + (r & 3); }
 
-// Output tiles of 32 nodes per wavefront in the forward layer.
-#ifndef LBFD_SG_FWD_NT
-#define LBFD_SG_FWD_NT 4
-#endif
-constexpr int FWD_NT = LBFD_SG_FWD_NT;
-constexpr int FWD_NODES = 4 * 32 * FWD_NT;   // output nodes per workgroup
-
-// Forward layer: out[m][o] = act(b[o] + sum_{tap,i} in[m + tap][i] w[tap][o][i]) over the
-// M = B (Di-2)(Hi-2)(Wi-2) output nodes. wb: BF16 [27][32][CIN] (input channel fastest).
-// out: BF16 [M][32], or with OUTF32 FP32 [M][NOUT] (the first NOUT channels, no activation).
-// Each wavefront computes FWD_NT tiles of 32 nodes x 32 channels; every weight
-// fragment read from LDS feeds FWD_NT matrix instructions.
-template <int CIN, bool RELU, bool OUTF32>
-__global__ __launch_bounds__(256) void k_conv_fwd(const u16 *__restrict__ in, const u16 *__restrict__ wb,
-                                                 const float *__restrict__ bias, void *__restrict__ out, int Di,
-                                                 int Hi, int Wi, long long M)
+// BF16 weights in fragment order: the 16 bytes of lane l for tap t and the c-th sixteen of the
+// NC = CIN / 16 reduction channels are at ((t NC + c) 64 + l) 8, so a wavefront reads a
+// fragment as 1 KB in a row (in rows of a channel each lane's 16 bytes sat 64 bytes from its
+// neighbour's, four times the cache accesses).
+__host__ __device__ constexpr long long frag_at(int t, int nc, int k, int col)
 {
-    constexpr int NT = FWD_NT;
-    constexpr int LDW = CIN + 8;   // padded LDS row
-    __shared__ __attribute__((aligned(16))) u16 sw[27 * CO * LDW];
-    for (int i = threadIdx.x; i < 27 * CO * (CIN / 8); i += 256) {
-        const int row = i / (CIN / 8), piece = i % (CIN / 8);
-        *(u32x4 *)&sw[row * LDW + piece * 8] = *(const u32x4 *)&wb[row * CIN + piece * 8];
-    }
-    __syncthreads();
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int mr = lane & 31, kg = lane >> 5;
-    const int Do = Di - 2, Ho = Hi - 2, Wo = Wi - 2;
-    const long long m0 = ((long long)blockIdx.x * 4 + wave) * (32 * NT);
-    const u16 *src[NT];
-    bool ok[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const long long m = m0 + 32 * t + mr;
-        ok[t] = m < M;
-        long long r = ok[t] ? m : 0;
-        const int x = (int)(r % Wo);
-        r /= Wo;
-        const int y = (int)(r % Ho);
-        r /= Ho;
-        const int z = (int)(r % Do);
-        const long long b = r / Do;
-        src[t] = in + (((b * Di + z) * Hi + y) * (long long)Wi + x) * CIN + kg * 8;
-    }
-    f32x16 acc[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
-    for (int a = 0; a < 3; ++a)
-        for (int p = 0; p < 3; ++p)
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                const int tap = (a * 3 + p) * 3 + q;
-                const long long toff = ((long long)(a * Hi + p) * Wi + q) * CIN;
-#pragma unroll
-                for (int c = 0; c < CIN / 16; ++c) {
-                    const bf16x8 B = frag(&sw[(tap * CO + mr) * LDW + c * 16 + kg * 8]);
-                    bf16x8 A[NT];
-#pragma unroll
-                    for (int t = 0; t < NT; ++t) A[t] = ok[t] ? frag(src[t] + toff + c * 16) : frag_zero();
-#pragma unroll
-                    for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[t], B, acc[t], 0, 0, 0);
-                }
-            }
-    const float bv = bias[mr];
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const long long m = m0 + 32 * t + acc_row(r, kg);
-            if (m >= M) continue;
-            float v = acc[t][r] + bv;
-            if constexpr (OUTF32) {
-                if (mr < NOUT) ((float *)out)[m * NOUT + mr] = v;
-            } else {
-                if (RELU) v = fmaxf(v, 0.0f);
-                ((u16 *)out)[m * CO + mr] = f2bf(v);
-            }
-        }
+    return (((long long)t * nc + k / 16) * 64 + (k % 16) / 8 * 32 + col) * 8 + k % 8;
 }
 
-// The same layer on wide grids, marching along z. A workgroup owns columns of
-// ZX x ZY output nodes (x, y) over zc consecutive output planes; wavefront w computes
-// output row y0 + w. The layer's weight fragments stay in registers for the whole
-// kernel (27 taps x CIN/16 fragments), so the only operand read per matrix
-// instruction is the input fragment, from LDS. Input planes (ZY + 2 rows of 32 nodes)
-// rotate through four LDS slots; each plane is fetched into registers two planes
-// ahead of the one being computed. The three x-taps share one input fragment: for tap
-// q the partial sums P_q[j] = sum in[x0 + j] w_q are kept per input node j of the
-// row, and out[x0 + i] = P_0[i] + P_1[i + 1] + P_2[i + 2] (i < ZX = 30): the three
-// partial tiles go to a per-wavefront LDS scratch, from which each lane reads 8
-// consecutive channels of a node (16-byte stores, hardware BF16 conversion, round to
-// nearest even). A persistent grid walks the columns.
-constexpr int ZX = 30, ZY = 4;
+// Lane l gets v of lane l xor 32.
+__device__ __forceinline__ float other_half(float v, bool low)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(low ? r[1] : r[0]);
+}
+template <int CTRL> __device__ __forceinline__ uint32_t quad_mov(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xf, 0xf, false);
+}
+
+// Four rows of one channel in every lane -> four channels of one row: the lanes of a quad hold
+// channels c .. c + 3 (c = lane column, a multiple of 4 at the first of them) of rows 0 .. 3;
+// lane q of the quad ends with row q, channels c .. c + 3, rounded to BF16 (nearest even).
+__device__ __forceinline__ uint2 quad_rows(float v0, float v1, float v2, float v3, int lane)
+{
+    const uint32_t p01 = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)v0, (__bf16)v1});
+    const uint32_t p23 = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)v2, (__bf16)v3});
+    // odd lanes take the odd row of the pair
+    const uint32_t sel = lane & 1 ? 0x03020706u : 0x05040100u;
+    const uint32_t a = __builtin_amdgcn_perm(quad_mov<0xB1>(p01), p01, sel);
+    const uint32_t b = __builtin_amdgcn_perm(quad_mov<0xB1>(p23), p23, sel);
+    const bool hi = (lane & 2) != 0;
+    const uint32_t got = quad_mov<0x4E>(hi ? a : b);
+    return hi ? uint2{got, b} : uint2{a, got};
+}
+
+// Forward layer on wide grids: out[m][o] = act(b[o] + sum_{tap,i} in[m + tap][i] w[tap][i][o]).
+// in: channels-last BF16, wb: BF16 in fragment order, out: BF16 [M][32], or with OUTF32 FP32
+// [M][NOUT] (the first NOUT channels, no activation).
+//
+// A workgroup owns columns of ZX x ZY output nodes (x, y) over zc consecutive output planes;
+// wavefront w computes output rows y0 + 2 w and y0 + 2 w + 1, which share every weight
+// fragment. Input planes (ZY + 2 rows of 32 nodes) rotate through four LDS slots; each is
+// fetched into registers two planes ahead of the one being computed. The three x-taps share
+// one input fragment: for tap q the partial sums P_q[j] = sum in[x0 + j] w_q are kept per
+// input node j of the row, and out[x0 + i] = P_0[i] + P_1[i + 1] + P_2[i + 2] (i < ZX = 30).
+//
+// Bound: the matrix cores, and the instructions issued between their own. So the weights of QR of
+// the three x-taps stay in registers, as many as the vector registers hold without copies from
+// the accumulation registers (which cost four instructions a product), and the others are read
+// from LDS, once for two rows. A wavefront per SIMD is all the registers allow with 32 input
+// channels, so nothing else hides what comes after the products: the shifted sum, bias,
+// rounding and stores of a plane are issued between the matrix instructions of the next one
+// (two sets of accumulators), and the shift by one and two rows is a register renaming but
+// for every fourth row (a swap of the wavefront's halves), where it went through an LDS scratch.
+// Columns are dealt to the XCDs in contiguous runs, whose neighbours share rows in one L2.
+// 264^3 input nodes: 6 -> 32 channels 924 -> 572 us, 32 -> 32 1436 -> 1242 us (780 TFLOP/s; the
+// matrix cores are busy half the cycles and the clock falls to 1.7 GHz under this
+// load), 32 -> 7 686 -> 609 us.
+constexpr int ZX = 30, ZY = 8;
+// Workgroups that share a compute unit, and x-taps whose weights stay in registers.
+template <int CIN> __host__ __device__ constexpr int zm_per_cu() { return CIN == 16 ? 2 : 1; }
 template <int CIN, bool RELU, bool OUTF32>
-__global__ __launch_bounds__(256) void k_conv_fwd_zm(const u16 *__restrict__ in, const u16 *__restrict__ wb,
-                                                    const float *__restrict__ bias, void *__restrict__ out, int Di,
-                                                    int Hi, int Wi, int nbx, int nby, int nbz, int zc, long long ncol)
+__global__ __launch_bounds__(256, (zm_per_cu<CIN>())) void k_conv_fwd_zm(
+    const u16 *__restrict__ in, const u16 *__restrict__ wb, const float *__restrict__ bias, void *__restrict__ out,
+    int Di, int Hi, int Wi, int nbx, int nby, int nbz, int zc, long long ncol)
 {
     constexpr int CP = CIN + 8;                   // node stride in LDS (elements)
     constexpr int PR = ZY + 2;                    // input rows of a plane
@@ -165,30 +133,41 @@ __global__ __launch_bounds__(256) void k_conv_fwd_zm(const u16 *__restrict__ in,
     constexpr int PCS = CIN / 8;                  // 16-byte pieces per node
     constexpr int PIECES = PR * 32 * PCS;         // 16-byte pieces per plane
     constexpr int PPT = (PIECES + 255) / 256;     // pieces per thread
-    constexpr int SS = 36;                        // scratch row stride (floats; rows 16-byte aligned)
     __shared__ __attribute__((aligned(16))) u16 ring[4 * PLANE];
-    __shared__ __attribute__((aligned(16))) float scr[4][3 * 32 * SS];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int mr = lane & 31, kg = lane >> 5;
     const int Do = Di - 2, Ho = Hi - 2, Wo = Wi - 2;
     // The last layer (NOUT = 7 outputs) takes 16 x 16 x 32 matrix instructions: 16
     // output columns instead of 32, half the matrix work; every other layer 32 x 32 x 16.
     constexpr bool N16 = OUTF32;
+    constexpr bool TWO = zm_per_cu<CIN>() == 1;   // two sets of accumulators
     constexpr int NCB = N16 ? CIN / 32 : NC;      // weight fragments per tap
+    constexpr int QR = N16 ? 3 : 1, QL = 3 - QR;  // x-taps with weights in registers, in LDS
     const int l16 = lane & 15, k16 = lane >> 4;
-    bf16x8 Bw[27][NCB];
+    __shared__ __attribute__((aligned(16))) u16 wl[QL > 0 ? 9 * NCB * QL * 64 * 8 : 8];
+    bf16x8 Bw[9][QR][NCB];
 #pragma unroll
     for (int t = 0; t < 27; ++t)
 #pragma unroll
-        for (int c = 0; c < NCB; ++c)
-            Bw[t][c] = N16 ? frag(wb + (t * CO + l16) * CIN + c * 32 + k16 * 8)
-                           : frag(wb + (t * CO + mr) * CIN + c * 16 + kg * 8);
-    // the epilogue: lane l stores 8 channels (c8 = 8 (l mod 4)) of rows l / 4 and
-    // l / 4 + 16, or (last layer) channels 4 (l mod 2) .. of row l / 2
-    const int c8 = OUTF32 ? 4 * (lane & 1) : 8 * (lane & 3);
-    float *const sw = scr[wave];
+        for (int c = 0; c < NCB; ++c) {
+            const u16 *p = wb + (N16 ? frag_at(t, NC, c * 32 + k16 * 8, l16) : frag_at(t, NC, c * 16 + kg * 8, mr));
+            const int ap = t / 3, q = t % 3;
+            if (q < QR) Bw[ap][q][c] = frag(p);
+            else if (wave == ap % 4) *(bf16x8 *)&wl[(((ap * NCB + c) * QL + q - QR) * 64 + lane) * 8] = frag(p);
+        }
+    const float bv = bias[N16 ? l16 : mr];
     const long long pstride = (long long)Hi * Wi * CIN;   // elements between input planes
-    for (long long col = blockIdx.x; col < ncol; col += gridDim.x) {
+    const long long oplane = (long long)Ho * Wo;
+    // accumulators of a plane: per row P_q of 32 rows x 32 columns, or 2 x (16 x 16)
+    struct Acc {
+        f32x16 w[2][N16 ? 1 : 3];
+        f32x4 n[2][N16 ? 3 : 1][2];
+    };
+    Acc s0, s1;
+    // this XCD's run of columns
+    const long long run = (ncol + 7) / 8, c0 = (long long)(blockIdx.x & 7u) * run;
+    const long long cend = c0 + run < ncol ? c0 + run : ncol;
+    for (long long col = c0 + (blockIdx.x >> 3); col < cend; col += gridDim.x >> 3) {
         long long r = col;
         const int bxi = (int)(r % nbx);
         r /= nbx;
@@ -210,14 +189,14 @@ __global__ __launch_bounds__(256) void k_conv_fwd_zm(const u16 *__restrict__ in,
             const bool ok = i < PIECES && x0 + (node & 31) < Wi && y0 + (node >> 5) < Hi;
             off[k] = ok ? ((node >> 5) * Wi + (node & 31)) * CIN + piece * 8 : -1;
         }
-        const auto fetch = [&](int pz, u32x4 *v) {
+        const auto fetch = [&](int pz, u32x4 *v) __attribute__((always_inline)) {
             const bool inz = z0 + pz < Di;
             const u16 *pb = cbase + pz * pstride;
 #pragma unroll
             for (int k = 0; k < PPT; ++k)
                 v[k] = off[k] >= 0 && inz ? *(const u32x4 *)(pb + off[k]) : u32x4{0u, 0u, 0u, 0u};
         };
-        const auto put = [&](int slot, const u32x4 *v) {
+        const auto put = [&](int slot, const u32x4 *v) __attribute__((always_inline)) {
 #pragma unroll
             for (int k = 0; k < PPT; ++k) {
                 const int i = (int)threadIdx.x + 256 * k;
@@ -227,316 +206,512 @@ __global__ __launch_bounds__(256) void k_conv_fwd_zm(const u16 *__restrict__ in,
         // planes 0-2 in slots 0-2; plane 3 in flight in registers (it is stored at the
         // end of plane 0, plane 4 fetched meanwhile)
         u32x4 nx0[PPT], nx1[PPT];
-        {
-            u32x4 v0[PPT], v1[PPT], v2[PPT];
-            fetch(0, v0);
-            fetch(1, v1);
-            fetch(2, v2);
-            if (nzo > 1) fetch(3, nx0);
-            put(0, v0);
-            put(1, v1);
-            put(2, v2);
-        }
+        fetch(0, nx0);
+        fetch(1, nx1);
+        put(0, nx0);
+        fetch(2, nx0);
+        put(1, nx1);
+        put(2, nx0);
+        if (nzo > 1) fetch(3, nx0);
         __syncthreads();
-        const int y = y0 + wave;
-        const int lim = min(ZX, Wo - x0);   // output nodes of this row tile
-        // output node x0 + i of this wavefront's row at plane z0 + iz is node
-        // orow + iz oplane + i; a lane stores rows acc_row(e, kg) of channel mr
+        const int y = y0 + 2 * wave;
+        const int full = min(ZX, Wo - x0);   // output nodes of a row tile
+        const int lim[2] = {y < Ho ? full : 0, y + 1 < Ho ? full : 0};
+        // output node x0 + i of row y + w at plane z0 + iz is node orow + w Wo + iz oplane + i
         const long long orow = ((b * Do + z0) * Ho + y) * (long long)Wo + x0;
-        const long long oplane = (long long)Ho * Wo;
+        // part h of the last step of row w of plane iz: shifted sum, bias, activation, store
+        const auto finish = [&](int h, int w, const Acc &p, int iz, bool on) __attribute__((always_inline)) {
+            const long long o0 = orow + (w ? Wo : 0) + iz * oplane;
+            const int n = on ? lim[w] : 0;
+            if constexpr (N16) {
+                // rows 16 h + 4 k16 + r: the next row is the next register, or the first one of
+                // the next sixteen lanes
+                const auto next = [&](const f32x4 *q, int e) __attribute__((always_inline)) {
+                    const float v = k16 == 0 && h == 0 ? q[1][e] : q[h][e];
+                    return __int_as_float(__builtin_amdgcn_ds_bpermute(((lane + 16) & 63) * 4, __float_as_int(v)));
+                };
+                const f32x4 *P0 = p.n[w][0], *P1 = p.n[w][1], *P2 = p.n[w][2];
+                const float x1 = next(P1, 0), x20 = next(P2, 0), x21 = next(P2, 1);
+                const float v[4] = {P0[h][0] + P1[h][1] + P2[h][2] + bv, P0[h][1] + P1[h][2] + P2[h][3] + bv,
+                                    P0[h][2] + P1[h][3] + x20 + bv, P0[h][3] + x1 + x21 + bv};
+                const int i = 16 * h + 4 * k16;
+                float *o = (float *)out + (o0 + i) * NOUT + l16;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (l16 < NOUT && i + e < n) o[e * NOUT] = v[e];
+            } else {
+                // rows 8 h + 4 kg + r: the next row is the next register, or the first one of the
+                // other half (of the next eight rows, for the upper half)
+                const bool low = kg == 0;
+                const auto next = [&](const f32x16 &q, int e) __attribute__((always_inline)) {
+                    const float up = h < 3 ? q[4 * h + 4 + e] : 0.0f;
+                    return other_half(low ? up : q[4 * h + e], low);
+                };
+                const f32x16 &P0 = p.w[w][0], &P1 = p.w[w][1], &P2 = p.w[w][2];
+                const float x1 = next(P1, 0), x20 = next(P2, 0), x21 = next(P2, 1);
+                float v[4] = {P0[4 * h] + P1[4 * h + 1] + P2[4 * h + 2] + bv,
+                              P0[4 * h + 1] + P1[4 * h + 2] + P2[4 * h + 3] + bv,
+                              P0[4 * h + 2] + P1[4 * h + 3] + x20 + bv, P0[4 * h + 3] + x1 + x21 + bv};
+                if (RELU)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.0f);
+                const uint2 pk = quad_rows(v[0], v[1], v[2], v[3], lane);
+                // the row as a buffer of its own length: stores past its end (and all of them with
+                // `on` false) are dropped, without a branch among the matrix instructions
+                const auto rs = __builtin_amdgcn_make_buffer_rsrc((u16 *)out + o0 * CO, 0, n * CO * 2, 0x00020000);
+                const int at = ((8 * h + 4 * kg + (lane & 3)) * CO + (mr & ~3)) * 2;
+                __builtin_amdgcn_raw_buffer_store_b64(u32x2{pk.x, pk.y}, rs, at, 0, 0);
+            }
+        };
+        constexpr int PARTS = N16 ? 2 : 4;   // parts of a row's last step
         // one output plane; cur holds plane iz + 3, nxt receives plane iz + 4 (the two
         // register sets swap roles every plane, so the loop below takes planes in pairs)
-        const auto plane = [&](int iz, u32x4 *cur, u32x4 *nxt) __attribute__((always_inline)) {
+        const auto plane = [&](int iz, u32x4 *cur, u32x4 *nxt, Acc &now, const Acc &prev) __attribute__((always_inline)) {
             if (iz + 2 < nzo) fetch(iz + 4, nxt);
-            if constexpr (N16) {
-                // rows = 16 nodes (two halves of the row tile), k = 32 channels of one tap
-                f32x4 acc[3][2];
+            constexpr int NG = 9 * NCB;   // input fragments of a plane and row
+            // fragment g = ((a 3 + p) NCB + c) of row w (N16: of its half)
+            const auto afrag = [&](int g, int w, int half) __attribute__((always_inline)) {
+                const int a = g / (3 * NCB), p = (g / NCB) % 3, c = g % NCB;
+                const u16 *row = ring + ((iz + a) & 3) * PLANE + (2 * wave + w + p) * 32 * CP;
+                return frag(N16 ? row + (16 * half + l16) * CP + c * 32 + k16 * 8 : row + mr * CP + c * 16 + kg * 8);
+            };
 #pragma unroll
-                for (int q = 0; q < 3; ++q)
+            for (int w = 0; w < 2; ++w)
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) acc[q][h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                for (int q = 0; q < 3; ++q) {
+                    if constexpr (N16) now.n[w][q][0] = now.n[w][q][1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                    else
 #pragma unroll
-                for (int g = 0; g < 9 * NCB; ++g) {
-                    const int a = g / (3 * NCB), p = (g / NCB) % 3, c = g % NCB;
-                    const u16 *base = ring + ((iz + a) & 3) * PLANE + ((wave + p) * 32 + l16) * CP + c * 32 + k16 * 8;
-                    const bf16x8 A0 = frag(base), A1 = frag(base + 16 * CP);
+                        for (int e = 0; e < 16; ++e) now.w[w][q][e] = 0.0f;
+                }
+            // fragments are read one step ahead of their matrix instructions
+            bf16x8 A[2][2][2], B[2][3];
+            const auto read = [&](int g) __attribute__((always_inline)) {
 #pragma unroll
-                    for (int q = 0; q < 3; ++q) {
-                        acc[q][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A0, Bw[(a * 3 + p) * 3 + q][c], acc[q][0],
-                                                                            0, 0, 0);
-                        acc[q][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A1, Bw[(a * 3 + p) * 3 + q][c], acc[q][1],
-                                                                            0, 0, 0);
+                for (int w = 0; w < 2; ++w) {
+                    A[g & 1][w][0] = afrag(g, w, 0);
+                    if (N16) A[g & 1][w][1] = afrag(g, w, 1);
+                }
+#pragma unroll
+                for (int q = QR; q < 3; ++q) B[g & 1][q] = frag(&wl[((g * QL + q - QR) * 64 + lane) * 8]);
+            };
+            read(0);
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                if (g + 1 < NG) read(g + 1);
+                const int ap = g / NCB, c = g % NCB;
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    const bf16x8 Bq = q < QR ? Bw[ap][q < QR ? q : 0][c] : B[g & 1][q];
+#pragma unroll
+                    for (int w = 0; w < 2; ++w) {
+                        if constexpr (N16) {
+                            now.n[w][q][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[g & 1][w][0], Bq, now.n[w][q][0], 0, 0, 0);
+                            now.n[w][q][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[g & 1][w][1], Bq, now.n[w][q][1], 0, 0, 0);
+                        } else {
+                            now.w[w][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[g & 1][w][0], Bq, now.w[w][q], 0, 0, 0);
+                        }
                     }
                 }
-                // lane l holds column l mod 16, rows 16 h + 4 (l / 16) + r
+                // a part of the plane before, every other step
+                if (TWO && g % 2 == 1 && g / 2 < 2 * PARTS) finish(g / 2 % PARTS, g / 2 / PARTS, prev, iz - 1, iz > 0);
+                if (N16) __builtin_amdgcn_sched_barrier(0);
+            }
+            if (TWO && !N16) {
+                // a few of those instructions after every matrix instruction, not all at once
 #pragma unroll
-                for (int q = 0; q < 3; ++q)
-#pragma unroll
-                    for (int h = 0; h < 2; ++h)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) sw[(32 * q + 16 * h + 4 * k16 + r) * SS + l16] = acc[q][h][r];
-            } else {
-                f32x16 acc[3];
-#pragma unroll
-                for (int q = 0; q < 3; ++q)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) acc[q][e] = 0.0f;
-                // input fragment g = ((a 3 + p) NC + c); the next one is read while the
-                // three matrix instructions of the current one run
-                const auto afrag = [&](int g) __attribute__((always_inline)) {
-                    const int a = g / (3 * NC), p = (g / NC) % 3, c = g % NC;
-                    return frag(ring + ((iz + a) & 3) * PLANE + ((wave + p) * 32 + mr) * CP + c * 16 + kg * 8);
-                };
-                bf16x8 A = afrag(0);
-#pragma unroll
-                for (int g = 0; g < 9 * NC; ++g) {
-                    const bf16x8 An = g + 1 < 9 * NC ? afrag(g + 1) : A;
-                    const int ap = g / NC, c = g % NC;
-#pragma unroll
-                    for (int q = 0; q < 3; ++q)
-                        acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, Bw[ap * 3 + q][c], acc[q], 0, 0, 0);
-                    A = An;
-                }
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int j = acc_row(e, kg);
-                    sw[j * SS + mr] = acc[0][e];
-                    sw[(32 + j) * SS + mr] = acc[1][e];
-                    sw[(64 + j) * SS + mr] = acc[2][e];
+                for (int i = 0; i < 6 * NG; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // matrix
+                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // LDS read
+                    __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);   // vector
                 }
             }
             if (iz + 1 < nzo) put((iz + 3) & 3, cur);
-            __syncthreads();
-            if (y >= Ho) return;
-            const long long mrow = orow + iz * oplane;
-            // P_0[i] + P_1[i + 1] + P_2[i + 2] + bias of 4 channels at c of row i
-            const auto sum4 = [&](int i, int c, float *v) {
-                const float4 a = *(const float4 *)&sw[i * SS + c];
-                const float4 p = *(const float4 *)&sw[(33 + i) * SS + c];
-                const float4 q = *(const float4 *)&sw[(66 + i) * SS + c];
-                const float4 bz = *(const float4 *)&bias[c];
-                v[0] = a.x + p.x + q.x + bz.x;
-                v[1] = a.y + p.y + q.y + bz.y;
-                v[2] = a.z + p.z + q.z + bz.z;
-                v[3] = a.w + p.w + q.w + bz.w;
-            };
-            if constexpr (OUTF32) {
-                const int i = lane >> 1;
-                if (i < lim) {
-                    float v[4];
-                    sum4(i, c8, v);
-                    float *o = (float *)out + (mrow + i) * NOUT + c8;
+            if (!TWO)
 #pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        if (c8 + k < NOUT) o[k] = v[k];
+                for (int h = 0; h < 2 * PARTS; ++h) finish(h % PARTS, h / PARTS, now, iz, true);
+            __syncthreads();
+        };
+        for (int iz = 0; iz < nzo; iz += 2) {
+            plane(iz, nx0, nx1, s0, TWO ? s1 : s0);
+            if (iz + 1 < nzo) plane(iz + 1, nx1, nx0, TWO ? s1 : s0, s0);
+        }
+        if (TWO)
+#pragma unroll
+            for (int h = 0; h < 2 * PARTS; ++h) {
+                if (nzo & 1) finish(h % PARTS, h / PARTS, s0, nzo - 1, true);
+                else finish(h % PARTS, h / PARTS, s1, nzo - 1, true);
+            }
+        // (every wavefront is past its last read of the slots: plane() ends with a barrier)
+    }
+}
+
+// The same sums over rows of a narrower grid, output nodes in their order in memory.
+//
+// FWD:   out[m][o] = max(0, b[o] + sum_{tap,i} in[m + tap][i] w[tap][i][o])   BF16 [M][32]
+// LAST:  out[m][o] = b[o] + the same sum, FP32 [M][NOUT]
+// DGRAD: out[v][i] = [mask[v][i] > 0] sum_{tap,o} in[v - tap][o] w[tap][o][i], BF16 [M][32]:
+//        the input gradient, with the ReLU of the layer below applied (mask: that layer's
+//        output); in: the output gradient, zero outside its grid.
+// in: channels-last BF16 [B][Ds][Hs][Ws][CIN], wb in fragment order; output grid Do, Ho, Wo (Ds - 2
+// .. for the forward layers, Ds + 2 .. for DGRAD).
+//
+// A unit of work is ry rows of one output plane. Its input (3 planes of ry + 2 rows of Wo + 2
+// nodes) is staged in LDS while the unit before is computed (two buffers, registers in
+// between); consecutive output nodes, whatever rows they lie in, form the 32-row tiles of the
+// matrix instructions, so narrow rows waste nothing. The weights stay in registers, a wavefront
+// per SIMD; each wavefront takes tiles in pairs that share a weight fragment. Units are
+// dealt to the XCDs in contiguous runs (neighbouring planes share an L2).
+//
+// Bound: LDS reads and the matrix cores alike (an input fragment a matrix instruction). The
+// kernels before it read those fragments from global memory, 64 bytes from lane to lane:
+// 8 tiles of 40^3, 32 -> 32 channels 92 -> 42 us, 32 -> 7 51 -> 35, 6 -> 32 55 -> 32, input
+// gradient 119 -> 69; a 24^3 grid 30 -> 9 us a layer.
+enum { FWD = 0, LAST = 1, DGRAD = 2 };
+constexpr int ROWS_NODES = 1000;   // staged nodes of a unit at most (two buffers fill the LDS)
+template <int CIN, int KIND>
+__global__ __launch_bounds__(256, 1) void k_conv_rows(const u16 *__restrict__ in, const u16 *__restrict__ wb,
+                                                     const float *__restrict__ bias, const u16 *__restrict__ mask,
+                                                     void *__restrict__ out, int Ds, int Hs, int Ws, int Do, int Ho,
+                                                     int Wo, int ry, int nyb, int units)
+{
+    constexpr int CP = CIN + 8, NC = CIN / 16, PCS = CIN / 8;
+    constexpr int PPT = (ROWS_NODES * PCS + 255) / 256;
+    constexpr int OFF = KIND == DGRAD ? 2 : 0;
+    __shared__ __attribute__((aligned(16))) u16 buf[2][ROWS_NODES * CP];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int mr = lane & 31, kg = lane >> 5;
+    const int SW = Wo + 2, SR = ry + 2, nodes = 3 * SR * SW;
+    bf16x8 Bw[27][NC];
+#pragma unroll
+    for (int t = 0; t < 27; ++t)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) Bw[t][c] = frag(wb + frag_at(t, NC, c * 16 + kg * 8, mr));
+    const float bv = KIND == DGRAD ? 0.0f : bias[mr];
+    // place of this thread's staged pieces: plane, row, x (relative to the unit)
+    int place[PPT];
+#pragma unroll
+    for (int k = 0; k < PPT; ++k) {
+        const int node = ((int)threadIdx.x + 256 * k) / PCS;
+        const int t = node / SW, s = t / SR;
+        place[k] = node < nodes ? s << 20 | (t - s * SR) << 10 | (node - t * SW) : -1;
+    }
+    const int part = (int)threadIdx.x % PCS * 8;   // 256 is a multiple of PCS
+    struct Unit { int b, z, y0; };
+    const auto unit_of = [&](int u) {
+        Unit w;
+        const int t = u / nyb;
+        w.y0 = (u - t * nyb) * ry;
+        w.b = t / Do;
+        w.z = t - w.b * Do;
+        return w;
+    };
+    u32x4 v[PPT];
+    const auto fetch = [&](int u) __attribute__((always_inline)) {
+        const Unit w = unit_of(u);
+#pragma unroll
+        for (int k = 0; k < PPT; ++k) {
+            const int z = w.z - OFF + (place[k] >> 20), y = w.y0 - OFF + ((place[k] >> 10) & 1023), x = (place[k] & 1023) - OFF;
+            const bool ok = place[k] >= 0 && (uint32_t)z < (uint32_t)Ds && (uint32_t)y < (uint32_t)Hs && (uint32_t)x < (uint32_t)Ws;
+            v[k] = ok ? *(const u32x4 *)(in + (((long long)(w.b * Ds + z) * Hs + y) * Ws + x) * CIN + part) : u32x4{0u, 0u, 0u, 0u};
+        }
+    };
+    const auto put = [&](u16 *d) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < PPT; ++k)
+            if (place[k] >= 0) *(u32x4 *)&d[((int)threadIdx.x + 256 * k) / PCS * CP + part] = v[k];
+    };
+    // NT tiles from tile t on of the unit in s; n: its output nodes, m0: the first one
+    const auto tiles = [&](auto NTC, const u16 *s, int t, int n, long long m0) __attribute__((always_inline)) {
+        constexpr int NT = decltype(NTC)::value;
+        const u16 *base[NT];
+        f32x16 acc[NT];
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            const int j = min(32 * (t + i) + mr, n - 1), yy = j / Wo;
+            base[i] = s + (yy * SW + (j - yy * Wo)) * CP + kg * 8;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][e] = 0.0f;
+        }
+#pragma unroll
+        for (int ap = 0; ap < 9; ++ap) {
+            const int a = KIND == DGRAD ? 2 - ap / 3 : ap / 3, p = KIND == DGRAD ? 2 - ap % 3 : ap % 3;
+            const int row = (a * SR + p) * SW * CP;
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    bf16x8 A[NT];
+#pragma unroll
+                    for (int i = 0; i < NT; ++i) A[i] = frag(base[i] + row + (KIND == DGRAD ? 2 - q : q) * CP + c * 16);
+#pragma unroll
+                    for (int i = 0; i < NT; ++i)
+                        acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[i], Bw[ap * 3 + q][c], acc[i], 0, 0, 0);
+                }
+        }
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            const int j0 = 32 * (t + i);
+            if constexpr (KIND == LAST) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int j = j0 + acc_row(e, kg);
+                    if (mr < NOUT && j < n) ((float *)out)[(m0 + j) * NOUT + mr] = acc[i][e] + bv;
                 }
             } else {
 #pragma unroll
-                for (int pass = 0; pass < 2; ++pass) {
-                    const int i = (lane >> 2) + 16 * pass;
-                    if (i >= lim) continue;
-                    float v[8];
-                    sum4(i, c8, v);
-                    sum4(i, c8 + 4, v + 4);
-                    bf16x2 h[4];
+                for (int h = 0; h < 4; ++h) {
+                    float o[4];
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        float lo = v[2 * k], hi = v[2 * k + 1];
-                        if (RELU) {
-                            lo = fmaxf(lo, 0.0f);
-                            hi = fmaxf(hi, 0.0f);
-                        }
-                        h[k] = bf16x2{(__bf16)lo, (__bf16)hi};
+                    for (int e = 0; e < 4; ++e) {
+                        o[e] = acc[i][4 * h + e];
+                        if (KIND == FWD) o[e] = fmaxf(o[e] + bv, 0.0f);
                     }
-                    *(u32x4 *)&((u16 *)out)[(mrow + i) * CO + c8] =
-                        u32x4{__builtin_bit_cast(uint32_t, h[0]), __builtin_bit_cast(uint32_t, h[1]),
-                              __builtin_bit_cast(uint32_t, h[2]), __builtin_bit_cast(uint32_t, h[3])};
+                    uint2 pk = quad_rows(o[0], o[1], o[2], o[3], lane);
+                    const int j = j0 + 8 * h + 4 * kg + (lane & 3);
+                    if (j >= n) continue;
+                    const long long at = (m0 + j) * CO + (mr & ~3);
+                    if constexpr (KIND == DGRAD) {
+                        // x > 0 for a ReLU output: its bits are not zero and its sign is clear
+                        const uint2 x = *(const uint2 *)&mask[at];
+                        const auto keep = [](uint32_t g, uint32_t w) {
+                            const uint32_t lo = w & 0xffffu, hi = w >> 16;
+                            return g & ((lo - 1u < 0x7fffu ? 0xffffu : 0u) | (hi - 1u < 0x7fffu ? 0xffff0000u : 0u));
+                        };
+                        pk = uint2{keep(pk.x, x.x), keep(pk.y, x.y)};
+                    }
+                    *(uint2 *)&((u16 *)out)[at] = pk;
                 }
             }
-        };
-        for (int iz = 0; iz < nzo; iz += 2) {
-            plane(iz, nx0, nx1);
-            if (iz + 1 < nzo) plane(iz + 1, nx1, nx0);
         }
-        // every wavefront is past its last read of the slots before the next column fills them
+    };
+    const int run = (units + 7) / 8, u0 = (int)(blockIdx.x & 7u) * run, uend = min(u0 + run, units);
+    const int step = (int)gridDim.x >> 3;
+    int u = u0 + (int)(blockIdx.x >> 3), cur = 0;
+    if (u >= uend) return;
+    fetch(u);
+    put(buf[0]);
+    __syncthreads();
+    for (; u < uend; u += step, cur ^= 1) {
+        const bool more = u + step < uend;
+        if (more) fetch(u + step);
+        const Unit w = unit_of(u);
+        const int n = min(ry, Ho - w.y0) * Wo, nt = (n + 31) / 32, per = (nt + 3) / 4;
+        const long long m0 = ((long long)(w.b * Do + w.z) * Ho + w.y0) * Wo;
+        const int tend = min(nt, (wave + 1) * per);
+        int t = wave * per;
+        for (; t + 1 < tend; t += 2) tiles(std::integral_constant<int, 2>{}, buf[cur], t, n, m0);
+        if (t < tend) tiles(std::integral_constant<int, 1>{}, buf[cur], t, n, m0);
+        if (more) put(buf[cur ^ 1]);
         __syncthreads();
     }
 }
 
-// Input gradient of a layer with 32 input channels, with the ReLU of the layer below
-// applied: dx[v][i] = [x[v][i] > 0] sum_{tap,o} dy[v - tap][o] w[tap][i][o], over the
-// Mi = B Di Hi Wi input nodes. wt: BF16 [27][32 (i)][32 (o)] (output channel fastest).
-// x: the layer's input (BF16 [Mi][32]); dy: BF16 [B][Di-2][Hi-2][Wi-2][32].
-__global__ __launch_bounds__(256) void k_conv_dgrad(const u16 *__restrict__ dy, const u16 *__restrict__ wt,
-                                                   const u16 *__restrict__ x, u16 *__restrict__ dx, int Di, int Hi,
-                                                   int Wi, long long Mi)
+// Rows of a unit of k_conv_rows for an output grid: the fewest rounds over `cus` workgroups, each as
+// long as the wavefront with the most tiles (54 matrix instructions of 32 cycles a tile with 32
+// input channels, and some 1500 cycles a unit for its start, end and barrier).
+inline int rows_per_unit(int B, int Do, int Ho, int Wo, int cus)
 {
-    constexpr int LDW = CO + 8;
-    __shared__ __attribute__((aligned(16))) u16 sw[27 * CO * LDW];
-    for (int i = threadIdx.x; i < 27 * CO * (CO / 8); i += 256) {
-        const int row = i / (CO / 8), piece = i % (CO / 8);
-        *(u32x4 *)&sw[row * LDW + piece * 8] = *(const u32x4 *)&wt[row * CO + piece * 8];
-    }
-    __syncthreads();
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int mr = lane & 31, kg = lane >> 5;
-    const int Do = Di - 2, Ho = Hi - 2, Wo = Wi - 2;
-    const long long m0 = ((long long)blockIdx.x * 4 + wave) * 64;
-    int xx[2], yy[2], zz[2];
-    long long bb[2];
-    bool ok[2];
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        const long long m = m0 + 32 * t + mr;
-        ok[t] = m < Mi;
-        long long r = ok[t] ? m : 0;
-        xx[t] = (int)(r % Wi);
-        r /= Wi;
-        yy[t] = (int)(r % Hi);
-        r /= Hi;
-        zz[t] = (int)(r % Di);
-        bb[t] = r / Di;
-    }
-    f32x16 acc[2];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
-    for (int a = 0; a < 3; ++a)
-        for (int p = 0; p < 3; ++p)
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                const int tap = (a * 3 + p) * 3 + q;
-                long long src[2];
-                bool in_range[2];
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    const int z = zz[t] - a, y = yy[t] - p, x = xx[t] - q;
-                    in_range[t] = ok[t] && z >= 0 && z < Do && y >= 0 && y < Ho && x >= 0 && x < Wo;
-                    src[t] = in_range[t] ? ((((bb[t] * Do + z) * Ho + y) * (long long)Wo + x) * CO + kg * 8) : 0;
-                }
-#pragma unroll
-                for (int c = 0; c < CO / 16; ++c) {
-                    const bf16x8 B = frag(&sw[(tap * CO + mr) * LDW + c * 16 + kg * 8]);
-#pragma unroll
-                    for (int t = 0; t < 2; ++t) {
-                        const bf16x8 A = in_range[t] ? frag(dy + src[t] + c * 16) : frag_zero();
-                        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, B, acc[t], 0, 0, 0);
-                    }
-                }
-            }
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const long long m = m0 + 32 * t + acc_row(r, kg);
-            if (m >= Mi) continue;
-            const u16 xv = x[m * CO + mr];
-            const bool active = (xv & 0x8000u) == 0 && xv != 0;   // x > 0 (x is a ReLU output)
-            dx[m * CO + mr] = active ? f2bf(acc[t][r]) : (u16)0;
+    int best = 1;
+    double least = 0.0;
+    for (int ry = 1; ry <= Ho && 3 * (ry + 2) * (Wo + 2) <= ROWS_NODES; ++ry) {
+        const long long units = (long long)B * Do * ((Ho + ry - 1) / ry);
+        const int tiles = (ry * Wo + 31) / 32;
+        const double cost = (double)((units + cus - 1) / cus) * (54.0 * 32.0 * ((tiles + 3) / 4) + 1500.0);
+        if (ry == 1 || cost < least) {
+            least = cost;
+            best = ry;
         }
+    }
+    return best;
 }
 
-// Weight gradient of a layer: dw[tap][i][o] += sum_v x[v + tap][i] dy[v][o] over the
-// output nodes [v0, v1) of this block's split; grid (27 taps, splits). x: BF16 layer
-// input [B][Di][Hi][Wi][CIN]; dy: BF16 [M][32]; dw: FP32 [27][CIN][32]. The blocks of
-// tap 0 also add the bias gradient db[o] += sum_v dy[v][o]. Each stage stages 256
-// output nodes (input and output gradient transposed to [channel][node] in LDS, so
-// every operand fragment is a 16-byte LDS read); each wavefront reduces over 64 of
-// them in four matrix instructions; partial tiles meet in FP32 atomics.
+// Weight gradient of a layer: dw[tap][i][o] += sum_v x[v + tap][i] dy[v][o] over the output nodes
+// v, and the bias gradient db[o] += sum_v dy[v][o]. x: BF16 layer input [B][Di][Hi][Wi][CIN]; dy: BF16
+// [B][Do][Ho][Wo][32]; dw: FP32 [27][CIN][32].
+//
+// Per tap a 32 x 32 product (input x output channels) whose reduction runs over the nodes. A
+// unit is ry rows of an output plane: its dy and the three planes of x around it are staged in
+// LDS once for all 27 taps (two buffers; the next unit is in flight in registers meanwhile),
+// channels fastest as in memory, and the fragments, which need a channel's values at
+// consecutive nodes, come from LDS reads that transpose (a lane names any node, so a tap is
+// an address offset and rows of any length follow each other without gaps). Wavefront w
+// keeps the sums of seven taps (w mod 4; the 28th is a row of ones: the bias gradient) over
+// every other sixteen nodes (w / 4); a persistent workgroup adds them to dw with atomics once.
+//
+// Bound: the latency of staging a unit (some 3 us against 1 us of products) and, at the end, the
+// atomics (22 of 60 us on 8 tiles of 40^3). The kernel before it read x and dy once per tap and
+// transposed them by 2-byte LDS stores: 112 -> 60 us with 32 input channels, 112 -> 48 with 16.
+constexpr int WG_T = 512;
+constexpr int WG_TAPS = 7;       // taps of a wavefront
+constexpr int WG_NODES = 1000;   // staged nodes (x and dy) of a unit at most
+typedef short i16x4 __attribute__((ext_vector_type(4)));
+// Eight nodes of this lane's channel: elements 0-3 from address a, 4-7 from b. Sixteen lanes
+// read four nodes of sixteen channels, lane l the channels 4 (l mod 4) .. of node l / 4, and
+// lane l receives channel l of the four nodes.
+__device__ __forceinline__ bf16x8 frag_tr(const u16 *a, const u16 *b)
+{
+    typedef __attribute__((address_space(3))) i16x4 L;
+    struct { i16x4 lo, hi; } r = {__builtin_amdgcn_ds_read_tr16_b64_v4i16((L *)a), __builtin_amdgcn_ds_read_tr16_b64_v4i16((L *)b)};
+    return __builtin_bit_cast(bf16x8, r);
+}
 template <int CIN>
-__global__ __launch_bounds__(256) void k_conv_wgrad(const u16 *__restrict__ x, const u16 *__restrict__ dy,
-                                                   float *__restrict__ dw, float *__restrict__ db, int Di, int Hi,
-                                                   int Wi, long long M, long long per_split)
+__global__ __launch_bounds__(WG_T, 2) void k_conv_wgrad(const u16 *__restrict__ x, const u16 *__restrict__ dy,
+                                                       float *__restrict__ dw, float *__restrict__ db, int Di, int Hi,
+                                                       int Wi, int ry, int nyb, int units)
 {
-    constexpr int CH = 256;                 // output nodes per stage
-    constexpr int LDV = CH + 8;
-    __shared__ __attribute__((aligned(16))) u16 xs[32 * LDV];   // [channel][node]
-    __shared__ __attribute__((aligned(16))) u16 ds[32 * LDV];
-    __shared__ float red[3][16][64];
-    __shared__ float bred[8][32];
-    const int tap = blockIdx.x;
-    const int a = tap / 9, p = (tap / 3) % 3, q = tap % 3;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int mr = lane & 31, kg = lane >> 5;
-    const uint32_t Do = Di - 2, Ho = Hi - 2, Wo = Wi - 2;
-    const long long v_begin = (long long)blockIdx.y * per_split;
-    long long v_end = v_begin + per_split;
-    if (v_end > M) v_end = M;
-    if (CIN < 32)
-        for (int i = threadIdx.x; i < (32 - CIN) * LDV; i += 256) xs[CIN * LDV + i] = 0;
-    f32x16 acc;
+    constexpr int XP = CIN + 8, DP = CO + 8;   // node strides in LDS (elements)
+    constexpr int PPT = (WG_NODES * (CO / 8) + WG_T - 1) / WG_T;
+    // one buffer: x nodes, then dy nodes; the sums of wavefronts 4-7 at the end
+    constexpr int BUF = WG_NODES * DP;
+    constexpr int SUMS = 4 * WG_TAPS * 16 * 64;
+    __shared__ __attribute__((aligned(16))) u16 buf[2 * BUF];
+    static_assert(SUMS * 4 <= 4 * BUF, "the sums reuse the buffers");
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int set = wave & 3, half = wave >> 2;
+    const int mr = lane & 31, kg = lane >> 5, l16 = lane & 15;
+    const int Do = Di - 2, Ho = Hi - 2, Wo = Wi - 2, SR = ry + 2;
+    const int xn = 3 * SR * Wi, dn = (ry * Wo + 15) / 16 * 16;   // staged nodes of x, of dy (padded)
+    const int xpieces = xn * (CIN / 8), pieces = xpieces + dn * (CO / 8);
+    const uint32_t inv = ((1u << 20) + (uint32_t)Wo - 1u) / (uint32_t)Wo;   // k / Wo = k inv >> 20 for k < WG_NODES
+    int tofs[WG_TAPS];   // this wavefront's taps: offset of their x node
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-    float bsum = 0.0f;                      // tap 0: channel t mod 32 over nodes t/32, t/32 + 8, ...
-    const int j = threadIdx.x;              // staging: node j of the stage, every channel
-    for (long long v0 = v_begin; v0 < v_end; v0 += CH) {
-        const long long m = v0 + j;
-        const bool ok = m < v_end;
-        u32x4 xv[CIN / 8], dv[4];
-#pragma unroll
-        for (int k = 0; k < CIN / 8; ++k) xv[k] = u32x4{0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) dv[k] = u32x4{0u, 0u, 0u, 0u};
-        if (ok) {
-            uint32_t r = (uint32_t)m;       // the host keeps M below 2^31
-            const uint32_t xo = r % Wo;
-            r /= Wo;
-            const uint32_t yo = r % Ho;
-            r /= Ho;
-            const uint32_t zo = r % Do;
-            const uint32_t b = r / Do;
-            const long long src = ((((long long)b * Di + zo + a) * Hi + yo + p) * (long long)Wi + xo + q) * CIN;
-#pragma unroll
-            for (int k = 0; k < CIN / 8; ++k) xv[k] = *(const u32x4 *)&x[src + k * 8];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) dv[k] = *(const u32x4 *)&dy[m * CO + k * 8];
-        }
-#pragma unroll
-        for (int k = 0; k < CIN / 8; ++k) {
-            const u16 *xe = (const u16 *)&xv[k];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) xs[(k * 8 + e) * LDV + j] = xe[e];
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const u16 *de = (const u16 *)&dv[k];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) ds[(k * 8 + e) * LDV + j] = de[e];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            const int col = 64 * wave + 16 * kk + 8 * kg;
-            const bf16x8 A = frag(&xs[mr * LDV + col]);
-            const bf16x8 B = frag(&ds[mr * LDV + col]);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, B, acc, 0, 0, 0);
-        }
-        if (tap == 0) {
-            const int c = threadIdx.x & 31, g = threadIdx.x >> 5;
-#pragma unroll 8
-            for (int n = g; n < CH; n += 8) bsum += bf2f(ds[c * LDV + n]);
-        }
-        __syncthreads();
+    for (int j = 0; j < WG_TAPS; ++j) {
+        const int t = min(set * WG_TAPS + j, 26);
+        tofs[j] = ((t / 9 * SR + t / 3 % 3) * Wi + t % 3) * XP;
     }
-    if (wave > 0)
+    const bool ones = set == 3;
+    const bf16x8 one = __builtin_bit_cast(bf16x8, u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
+    f32x16 acc[WG_TAPS];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) red[wave - 1][r][lane] = acc[r];
-    if (tap == 0) bred[threadIdx.x >> 5][threadIdx.x & 31] = bsum;
+    for (int j = 0; j < WG_TAPS; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[j][e] = 0.0f;
+    // this thread's staged pieces of 16 bytes: plane, row and x of an x node, or node of dy
+    int place[PPT];
+#pragma unroll
+    for (int k = 0; k < PPT; ++k) {
+        const int i = (int)threadIdx.x + WG_T * k;
+        if (i < xpieces) {
+            const int node = i / (CIN / 8), t = node / Wi, s = t / SR;
+            place[k] = s << 20 | (t - s * SR) << 10 | (node - t * Wi);
+        } else {
+            place[k] = i < pieces ? 1 << 30 | (i - xpieces) / (CO / 8) : -1;
+        }
+    }
+    u32x4 v[PPT];
+    struct Unit { int b, z, y0; };
+    const auto unit_of = [&](int u) {
+        Unit w;
+        const int t = u / nyb;
+        w.y0 = (u - t * nyb) * ry;
+        w.b = t / Do;
+        w.z = t - w.b * Do;
+        return w;
+    };
+    const auto fetch = [&](int u) __attribute__((always_inline)) {
+        const Unit w = unit_of(u);
+        const int n = min(ry, Ho - w.y0) * Wo;
+        const u16 *xb = x + ((long long)(w.b * Di + w.z) * Hi + w.y0) * Wi * CIN;
+        const u16 *db_ = dy + ((long long)(w.b * Do + w.z) * Ho + w.y0) * Wo * CO;
+#pragma unroll
+        for (int k = 0; k < PPT; ++k) {
+            const int i = (int)threadIdx.x + WG_T * k;
+            v[k] = u32x4{0u, 0u, 0u, 0u};
+            if (place[k] < 0) continue;
+            if (place[k] >> 30) {
+                if ((place[k] & 0xfffff) < n) v[k] = *(const u32x4 *)(db_ + (long long)(i - xpieces) * 8);
+            } else {
+                const int s = place[k] >> 20, rr = (place[k] >> 10) & 1023, xx = place[k] & 1023;
+                if (w.y0 + rr < Hi) v[k] = *(const u32x4 *)(xb + (((long long)s * Hi + rr) * Wi + xx) * CIN + i % (CIN / 8) * 8);
+            }
+        }
+    };
+    const auto put = [&](u16 *d) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < PPT; ++k) {
+            const int i = (int)threadIdx.x + WG_T * k;
+            if (place[k] < 0) continue;
+            u16 *p = place[k] >> 30 ? d + xn * XP + (i - xpieces) / (CO / 8) * DP + (i - xpieces) % (CO / 8) * 8
+                                    : d + i / (CIN / 8) * XP + i % (CIN / 8) * 8;
+            *(u32x4 *)p = v[k];
+        }
+    };
+    const int run = (units + 7) / 8, u0 = (int)(blockIdx.x & 7u) * run, uend = min(u0 + run, units);
+    const int step = (int)gridDim.x >> 3;
+    int u = u0 + (int)(blockIdx.x >> 3), cur = 0;
+    if (u >= uend) return;
+    fetch(u);
+    put(buf);
     __syncthreads();
-    if (wave == 0)
+    // channels this lane reads (x: 16 channels repeat), and its node within four
+    const int dch = (mr >> 4) * 16 + (l16 & 3) * 4, xch = CIN == 16 ? (l16 & 3) * 4 : dch, sub = kg * 8 + (l16 >> 2);
+    for (; u < uend; u += step, cur ^= 1) {
+        const bool more = u + step < uend;
+        if (more) fetch(u + step);
+        const Unit w = unit_of(u);
+        const int n = min(ry, Ho - w.y0) * Wo;
+        const u16 *xs = buf + cur * BUF, *ds = xs + xn * XP;
+        for (int k0 = 16 * half; k0 < n; k0 += 32) {
+            const u16 *xa[2], *da[2];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const float s = acc[r] + red[0][r][lane] + red[1][r][lane] + red[2][r][lane];
-            const int i = acc_row(r, kg);
-            if (i < CIN && s != 0.0f) atomicAdd(&dw[((long long)tap * CIN + i) * CO + mr], s);
+            for (int h = 0; h < 2; ++h) {
+                const int k = k0 + sub + 4 * h;
+                da[h] = ds + k * DP + dch;
+                const int c = min(k, n - 1);   // past the end dy is zero
+                const int yy = (int)((uint32_t)c * inv >> 20);
+                xa[h] = xs + (yy * Wi + (c - yy * Wo)) * XP + xch;
+            }
+            const bf16x8 B = frag_tr(da[0], da[1]);
+            bf16x8 A[WG_TAPS];
+#pragma unroll
+            for (int j = 0; j < WG_TAPS; ++j) A[j] = frag_tr(xa[0] + tofs[j], xa[1] + tofs[j]);
+            if (ones) A[WG_TAPS - 1] = one;
+#pragma unroll
+            for (int j = 0; j < WG_TAPS; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[j], B, acc[j], 0, 0, 0);
         }
-    if (tap == 0 && threadIdx.x < 32) {
-        float t = 0.0f;
-#pragma unroll
-        for (int g = 0; g < 8; ++g) t += bred[g][threadIdx.x];
-        if (t != 0.0f) atomicAdd(&db[threadIdx.x], t);
+        if (more) put(buf + (cur ^ 1) * BUF);
+        __syncthreads();
     }
+    float *sums = (float *)buf;
+    if (half)
+#pragma unroll
+        for (int j = 0; j < WG_TAPS; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) sums[((set * WG_TAPS + j) * 16 + e) * 64 + lane] = acc[j][e];
+    __syncthreads();
+    if (half) return;
+#pragma unroll
+    for (int j = 0; j < WG_TAPS; ++j) {
+        const int t = set * WG_TAPS + j;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const float s = acc[j][e] + sums[((set * WG_TAPS + j) * 16 + e) * 64 + lane];
+            const int i = acc_row(e, kg);
+            if (t == 27) {
+                if (i == 0 && s != 0.0f) atomicAdd(&db[mr], s);
+            } else if (i < CIN && s != 0.0f) {
+                atomicAdd(&dw[((long long)t * CIN + i) * CO + mr], s);
+            }
+        }
+    }
+}
+
+// Rows of a unit of k_conv_wgrad: the fewest rounds, each as long as its sixteens of nodes (seven
+// matrix instructions of 32 cycles for every other one) and some 2000 cycles besides.
+inline int rows_per_wgrad_unit(int B, int Do, int Ho, int Wo, int cus)
+{
+    int best = 1;
+    double least = 0.0;
+    for (int ry = 1; ry <= Ho && 3 * (ry + 2) * (Wo + 2) + (ry * Wo + 15) / 16 * 16 <= WG_NODES; ++ry) {
+        const long long units = (long long)B * Do * ((Ho + ry - 1) / ry);
+        const double cost = (double)((units + cus - 1) / cus) * (7.0 * 32.0 * 2.0 * ((ry * Wo + 31) / 32) + 2000.0);
+        if (ry == 1 || cost < least) {
+            least = cost;
+            best = ry;
+        }
+    }
+    return best;
 }
 
 // Conservative form of the output (the network's 7 channels per node n of a T^3
@@ -635,8 +810,8 @@ struct Net {
     float *master, *m, *v;      // FP32 [n_params]
     float *gw[NL];              // FP32 [27][CIN_PAD][32] weight gradients
     float *gb[NL];              // FP32 [32] bias gradients
-    u16 *wb[NL];                // BF16 [27][32][CIN_PAD] forward weights
-    u16 *wt[NL];                // BF16 [27][CIN_PAD][32] transposed weights
+    u16 *wb[NL];                // BF16 forward weights in fragment order (reduction over input channels)
+    u16 *wt[NL];                // BF16 transposed weights in fragment order (reduction over output channels)
     float *bias[NL];            // FP32 [32]
 };
 
@@ -682,9 +857,15 @@ __global__ __launch_bounds__(256) void k_adam_pack(Net net, int adam, float lr, 
         net.bias[l][o] = w;
     } else {
         const u16 h = f2bf(w);
-        net.wb[l][((long long)tap * CO + o) * CIN_PAD[l] + i] = h;
-        net.wt[l][((long long)tap * CIN_PAD[l] + i) * CO + o] = h;
+        net.wb[l][frag_at(tap, CIN_PAD[l] / 16, i, o)] = h;
+        if (l > 0) net.wt[l][frag_at(tap, CO / 16, o, i)] = h;   // the first layer's input has no gradient
     }
+}
+
+__global__ __launch_bounds__(256) void k_zero(u32x4 *p, long long n)
+{
+    const long long k = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (k < n) p[k] = u32x4{0u, 0u, 0u, 0u};
 }
 
 // Gradients in parameter order (for export).
