@@ -157,7 +157,7 @@ __device__ __forceinline__ void load_moments(const KP<typename P::R> &k, const t
     meq_sum<LAT, R>(k, rR, rB, uj, m);
 #pragma unroll
     for (int r = 0; r < L::Q; ++r)
-        if (!conserved_row<LAT>(r)) m[r] += to_real(ldu(fs + (long long)state_slot<LAT>(r) * k.N, n));
+        if (!conserved_row<LAT>(r)) m[r] += to_real(ldu(fs + (long long)state_slot<LAT>(r) * k.NS, n));
 }
 
 template <int LAT, class P>
@@ -174,7 +174,7 @@ __device__ __forceinline__ void store_moments(const KP<typename P::R> &k, typena
     for (int r = 0; r < L::Q; ++r)
         if (!conserved_row<LAT>(r)) {
             const R v = m[r] - mref[r];
-            stu(fs + (long long)state_slot<LAT>(r) * k.N, n, dz ? from_real_sr<S>(v, dz->next()) : from_real<S>(v));
+            stu(fs + (long long)state_slot<LAT>(r) * k.NS, n, dz ? from_real_sr<S>(v, dz->next()) : from_real<S>(v));
         }
 }
 
@@ -201,7 +201,7 @@ __device__ __forceinline__ void store_state(const KP<typename P::R> &k, typename
         store_moments<LAT, P>(k, fo, n, rR, rB, uj, m);
     } else {
 #pragma unroll
-        for (int i = 0; i < Q; ++i) fo[(long long)i * k.N + n] = f[i];
+        for (int i = 0; i < Q; ++i) fo[(long long)i * k.NS + n] = f[i];
     }
 }
 
@@ -212,7 +212,7 @@ template <int LAT, class P> __global__ __launch_bounds__(256) void k_init(KP<typ
     using L = Lat<LAT>;
     Node nd = node_id(k);
     if (!nd.ok) return;
-    const long long N = k.N, n = lin(k, nd.x, nd.y, nd.z);
+    const long long N = k.NS, n = lin(k, nd.x, nd.y, nd.z);
     R rN0, fR[QMAX], fB[QMAX], u0[3], f[QMAX];
     init_node<LAT, R>(k, in, nd.x, nd.y, nd.z, rN0, fR, fB, u0);
     R rR = 0, rB = 0, j[3] = {0, 0, 0};
@@ -246,7 +246,7 @@ __global__ __launch_bounds__(256) void k_import(KP<typename P::R> k, const doubl
     using L = Lat<LAT>;
     Node nd = node_id(k);
     if (!nd.ok) return;
-    const long long N = k.N, n = lin(k, nd.x, nd.y, nd.z);
+    const long long N = k.N, NS = k.NS, n = lin(k, nd.x, nd.y, nd.z);
     R rR = (R)rR_[n], rB = (R)rB_[n], j[3] = {0, 0, 0}, f[QMAX];
     for (int i = 0; i < L::Q; ++i) {
         f[i] = (R)f_[i * N + n];
@@ -255,9 +255,9 @@ __global__ __launch_bounds__(256) void k_import(KP<typename P::R> k, const doubl
     R rr = rR / k.rhoR0, bb = rB / k.rhoB0;
     R *mac = k.fld.mac[k.lev];
     mac[n] = rR;
-    mac[N + n] = rB;
-    mac[2 * N + n] = (rr - bb) / (rr + bb);
-    for (int d = 0; d < L::D; ++d) mac[(3 + d) * N + n] = j[d];
+    mac[NS + n] = rB;
+    mac[2 * NS + n] = (rr - bb) / (rr + bb);
+    for (int d = 0; d < L::D; ++d) mac[(3 + d) * NS + n] = j[d];
     store_state<LAT, P>(k, (S *)k.fld.f[k.fc], n, f, rR, rB, j);
     k.fld.psi[k.pc][n] = (R)psi[n];
     k.fld.phi[k.pc][n] = (R)phi[n];
@@ -375,7 +375,7 @@ template <int LAT, class P> __device__ __forceinline__ void geom_body(const KP<t
         if (tile == 0 && threadIdx.x == 0 && threadIdx.y == 0) k.fld.sc->tick += 1u;
     Node nd = node_at(k, tile);
     if (!nd.ok) return;
-    const long long N = k.N;
+    const long long N = k.NS;   // between planes
     const uint32_t n = node_index(k, nd);
     const R *rN = k.fld.mac[level] + 2 * N;
     const Nbhd nb = make_nbhd(k, nd.x, nd.y, nd.z);
@@ -420,7 +420,7 @@ __device__ __forceinline__ void force_body(const KP<typename P::R> &k, int tile,
     using L = Lat<LAT>;
     constexpr int D = L::D;
     Node nd = node_at(k, tile);
-    const long long N = k.N;
+    const long long N = k.NS;   // between planes
     const R *psiA = k.fld.psi[sa.pc];
     // the normal and psi of the tile and its halo staged in LDS (FP32 arithmetic)
     constexpr bool LDS = sizeof(R) == 4;
@@ -544,7 +544,7 @@ __device__ __forceinline__ void collide_body(const KP<typename P::R> &k, int til
     Node nd = node_at(k, tile);
     if (!nd.ok) return;
     const int x = nd.x, y = nd.y, z = nd.z;
-    const long long N = k.N;
+    const long long N = k.NS;   // between planes
     const uint32_t n = node_index(k, nd);
     const S *fin = (const S *)k.fld.f[sa.fc];
     S *fout = (S *)k.fld.f[1 - sa.fc];
@@ -706,7 +706,7 @@ __device__ __forceinline__ void collide_body(const KP<typename P::R> &k, int til
             if (i != 0) v += bo ? rf : R(0);
         }
         // one store: base at the lower plane of the pair (i, opp(i)), which are at most
-        // two planes apart, so the offset stays below 3 N elements
+        // two planes apart, so the offset stays below three plane strides
         const int lo = i < L::OPP[i] ? i : L::OPP[i];
         const uint32_t N32 = (uint32_t)N;
         const uint32_t dst = bo ? (uint32_t)(L::OPP[i] - lo) * N32 + n
@@ -816,7 +816,7 @@ __device__ __forceinline__ void macro_body(const KP<typename P::R> &k, int tile,
     }
     if (!nd.ok) return;
     const int x = nd.x, y = nd.y, z = nd.z;
-    const long long N = k.N;
+    const long long N = k.NS;   // between planes
     const uint32_t n = node_index(k, nd);
     const S *fin = (const S *)k.fld.f[1 - sa.fc];
     const Nbhd nb = make_nbhd(k, x, y, z);
@@ -968,7 +968,7 @@ template <int LAT, class P> __device__ __forceinline__ void fd_body(const KP<typ
     Node nd = node_at(k, tile);
     if (!nd.ok) return;
     const int x = nd.x, y = nd.y, z = nd.z;
-    const long long N = k.N;
+    const long long N = k.NS;   // between planes
     const uint32_t n = node_index(k, nd);
     const R s = (R)k.fld.sc->scale;
     const R *psiA = k.fld.psi[sa.pc], *phiA = k.fld.phi[sa.pc];
@@ -1842,7 +1842,7 @@ __global__ __launch_bounds__(256) void k_sg_features(KP<typename P::R> k, uint16
     if (t >= px * py * pz) return;
     const int xp = (int)(t % px), yp = (int)((t / px) % py), zp = (int)(t / (px * py));
     const int x = ((xp - 4) % nx + nx) % nx, y = ((yp - 4) % ny + ny) % ny, z = ((zp - 4) % nz + nz) % nz;
-    const long long N = k.N;
+    const long long N = k.NS;   // between planes
     const uint32_t n = (uint32_t)(x + nx * (y + ny * z));
     const double sc = k.fld.sc->scale;
     float c[8];
@@ -1896,7 +1896,7 @@ __global__ __launch_bounds__(256) void k_sg_tiles(KP<R> k, const uint16_t *feat,
         const uint32_t n = (uint32_t)((ox + i) + k.nx * ((oy + j) + (long long)k.ny * (oz + l)));
         const float ps = (float)(sc * (double)ld(k.fld.psi[k.pc], n)), ph = (float)(sc * (double)ld(k.fld.phi[k.pc], n));
         const float W = (float)(ld(k.fld.G[k.lev], n) + k.fd_eps);
-        const float X = (float)((R(1) - ld(k.fld.mac[k.lev] + 2 * k.N, n)) + k.fd_eps);
+        const float X = (float)((R(1) - ld(k.fld.mac[k.lev] + 2 * k.NS, n)) + k.fd_eps);
         float *o = tgt + ((long long)b * nout + t) * 4;
         o[0] = W * (ps - snap[2 * (long long)n]) * idpsi;
         o[1] = X * (ph - snap[2 * (long long)n + 1]) * idphi;
@@ -1920,7 +1920,7 @@ __global__ __launch_bounds__(256) void k_sg_apply(KP<R> k, const float *o, float
     if (n >= k.N) return;
     const uint32_t i = (uint32_t)n;
     const int x = (int)(n % k.nx), y = (int)((n / k.nx) % k.ny), z = (int)(n / ((long long)k.nx * k.ny));
-    const R *G = k.fld.G[k.lev], *rN = k.fld.mac[k.lev] + 2 * k.N;
+    const R *G = k.fld.G[k.lev], *rN = k.fld.mac[k.lev] + 2 * k.NS;
     const auto Wof = [&](uint32_t m) { return (float)(ld(G, m) + k.fd_eps); };
     const auto Xof = [&](uint32_t m) { return (float)((R(1) - ld(rN, m)) + k.fd_eps); };
     const float ratio = dpsi / dphi;
@@ -2012,7 +2012,7 @@ __device__ __forceinline__ void total_body(const KP<typename P::R> &k, int level
     for (long long n = (long long)blk * TOTAL_T + t; n < N; n += (long long)nblk * TOTAL_T) {
         const uint32_t i = (uint32_t)n;
         double G = (double)(ld(k.fld.G[level], i) + k.fd_eps);
-        double X = (double)((R(1) - ld(k.fld.mac[level] + 2 * N, i)) + k.fd_eps);
+        double X = (double)((R(1) - ld(k.fld.mac[level] + 2 * k.NS, i)) + k.fd_eps);
         R vp, vf;
         if (from_split) {
             // after the solve: its colour-split iterates become the new level in node order
@@ -2097,7 +2097,7 @@ __global__ __launch_bounds__(256) void k_obs_part(KP<typename P::R> k, int pass,
     v[17] = INFINITY;
     v[18] = -INFINITY;
     if (nd.ok) {
-        const long long N = k.N, n = lin(k, nd.x, nd.y, nd.z);
+        const long long N = k.NS, n = lin(k, nd.x, nd.y, nd.z);
         const double s = k.fld.sc->scale;
         const auto *mac = k.fld.mac[k.lev];
         double rR = mac[n], rB = mac[N + n], rN = mac[2 * N + n];
@@ -2182,7 +2182,7 @@ template <int LAT, class P> __global__ __launch_bounds__(256) void k_export(KP<t
     using L = Lat<LAT>;
     Node nd = node_id(k);
     if (!nd.ok) return;
-    const long long N = k.N, n = lin(k, nd.x, nd.y, nd.z);
+    const long long N = k.N, NS = k.NS, n = lin(k, nd.x, nd.y, nd.z);
     const R *mac = k.fld.mac[k.lev];
     const double s = k.fld.sc->scale;
     switch (field) {
@@ -2190,8 +2190,8 @@ template <int LAT, class P> __global__ __launch_bounds__(256) void k_export(KP<t
         const S *f = (const S *)k.fld.f[k.fc];
         if constexpr (P::DEV) {
             R m[L::Q], uj[3] = {0, 0, 0};
-            const R rR = mac[n], rB = mac[N + n];
-            for (int d = 0; d < L::D; ++d) uj[d] = mac[(3 + d) * N + n] / (rR + rB);
+            const R rR = mac[n], rB = mac[NS + n];
+            for (int d = 0; d < L::D; ++d) uj[d] = mac[(3 + d) * NS + n] / (rR + rB);
             load_moments<LAT, P>(k, f, n, rR, rB, uj, m);
             for (int i = 0; i < L::Q; ++i) {
                 R v = 0;
@@ -2199,15 +2199,15 @@ template <int LAT, class P> __global__ __launch_bounds__(256) void k_export(KP<t
                 out[i * N + n] = (double)v;
             }
         } else {
-            for (int j = 0; j < L::Q; ++j) out[j * N + n] = (double)to_real(f[j * N + n]);
+            for (int j = 0; j < L::Q; ++j) out[j * N + n] = (double)to_real(f[j * NS + n]);
         }
         break;
     }
     case LBFD_FIELD_RHOR: out[n] = mac[n]; break;
-    case LBFD_FIELD_RHOB: out[n] = mac[N + n]; break;
-    case LBFD_FIELD_RHON: out[n] = mac[2 * N + n]; break;
-    case LBFD_FIELD_U: for (int d = 0; d < L::D; ++d) out[d * N + n] = k.fld.u[d * N + n]; break;
-    case LBFD_FIELD_FORCE: for (int d = 0; d < L::D; ++d) out[d * N + n] = k.fld.F[d * N + n]; break;
+    case LBFD_FIELD_RHOB: out[n] = mac[NS + n]; break;
+    case LBFD_FIELD_RHON: out[n] = mac[2 * NS + n]; break;
+    case LBFD_FIELD_U: for (int d = 0; d < L::D; ++d) out[d * N + n] = k.fld.u[d * NS + n]; break;
+    case LBFD_FIELD_FORCE: for (int d = 0; d < L::D; ++d) out[d * N + n] = k.fld.F[d * NS + n]; break;
     case LBFD_FIELD_PSI: out[n] = s * (double)k.fld.psi[k.pc][n]; break;
     case LBFD_FIELD_PHI: out[n] = s * (double)k.fld.phi[k.pc][n]; break;
     case LBFD_FIELD_G: out[n] = k.fld.G[k.lev][n]; break;
@@ -2336,6 +2336,15 @@ struct Layout {
         part, sc, obs, total;
 };
 
+// Elements between the planes of an array with several (populations, macroscopic fields,
+// vectors). On grids with powers of two in their extents planes of N elements start at
+// the same place of the memory channels' interleave, so the up to 33 streams of a kernel
+// visit the same channels at the same time; an odd multiple of 128 elements (a line of 256
+// bytes in two-byte planes) between them ends that. 256^3 FP32: collide 920 -> 855 us;
+// 128 x 128 x 384 with BF16 populations: 216 -> 206 us. Grids with other extents
+// (320 x 240 x 200: 718 us) and the other kernels are the same with and without it.
+long long plane_stride(long long N) { return (N + 127) / 128 * 128 + 17 * 128; }
+
 Layout layout(const lbfd_params *p)
 {
     Layout L{};
@@ -2346,14 +2355,15 @@ Layout layout(const lbfd_params *p)
     const long long nblocks = (long long)((p->nx + BX - 1) / BX) * ((p->ny + BY - 1) / BY) * p->nz;
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o += align256(bytes); return at; };
-    for (int b = 0; b < 2; ++b) L.f[b] = take(sp * Q * N);
-    for (int b = 0; b < 2; ++b) L.mac[b] = take(sr * (3 + D) * N);
+    const long long NS = plane_stride(N);
+    for (int b = 0; b < 2; ++b) L.f[b] = take(sp * Q * NS);
+    for (int b = 0; b < 2; ++b) L.mac[b] = take(sr * (3 + D) * NS);
     L.desc = take(sr * ndesc * N);
     for (int b = 0; b < 2; ++b) L.G[b] = take(sr * N);
-    L.nrm = take(sr * D * N);
-    L.u = take(sr * D * N);
-    L.F = take(sr * D * N);
-    L.qf = take(sr * D * N);
+    L.nrm = take(sr * D * NS);
+    L.u = take(sr * D * NS);
+    L.F = take(sr * D * NS);
+    L.qf = take(sr * D * NS);
     L.sorres = take(sizeof(unsigned long long) * 2 * (RMAX_IDX + 1) * RSLOTS * RSTRIDE);
     L.sync = take(sizeof(SorSync));
     for (int b = 0; b < 2; ++b) L.psi[b] = take(sr * N);
@@ -2361,10 +2371,10 @@ Layout layout(const lbfd_params *p)
     L.Sp = take(sr * N);
     L.Bp = take(sr * N);
     // arrays of the implicit solve, two colour planes of ((nx + 1) / 2) ny nz entries each
-    const long long NS = 2LL * ((p->nx + 1) / 2) * p->ny * p->nz;
-    L.rhs2 = take(2 * sr * NS);
-    L.cs2 = take(2 * sr * NS);
-    L.cw2 = take(2 * sr * NS);
+    const long long NP = 2LL * ((p->nx + 1) / 2) * p->ny * p->nz;
+    L.rhs2 = take(2 * sr * NP);
+    L.cs2 = take(2 * sr * NP);
+    L.cw2 = take(2 * sr * NP);
     const size_t npart = (size_t)NRED * (size_t)nblocks;
     L.part = take(sizeof(double) * (npart > (size_t)TOTAL_BLOCKS ? npart : (size_t)TOTAL_BLOCKS));
     L.sc = take(sizeof(DevScalars));
@@ -2471,6 +2481,7 @@ template <class R> void fill_kp(KP<R> &k, const lbfd_params *p, char *ws, const 
     k.gx = (p->nx + BX - 1) / BX;
     k.gy[0] = p->ny; k.gy[1] = (p->ny + 1) / 2; k.gy[2] = (p->ny + 3) / 4;
     k.N = (long long)p->nx * p->ny * p->nz;
+    k.NS = plane_stride(k.N);
     for (int a = 0; a < 3; ++a) k.bc[a] = p->bc[a];
     for (int w = 0; w < 6; ++w)
         for (int a = 0; a < 3; ++a) k.wall_u[w][a] = (R)p->wall_u[w][a];
@@ -2793,7 +2804,7 @@ template <int LAT, class P> struct Impl {
         const int lev = k.lev;
         const size_t rb = sizeof(R) * (size_t)h->N;
         if (hipMemcpyAsync(k.fld.G[1 - lev], k.fld.G[lev], rb, hipMemcpyDeviceToDevice, h->stream) != hipSuccess ||
-            hipMemcpyAsync(k.fld.mac[1 - lev] + 2 * h->N, k.fld.mac[lev] + 2 * h->N, rb, hipMemcpyDeviceToDevice,
+            hipMemcpyAsync(k.fld.mac[1 - lev] + 2 * k.NS, k.fld.mac[lev] + 2 * k.NS, rb, hipMemcpyDeviceToDevice,
                            h->stream) != hipSuccess)
             return LBFD_EHIP;
         for (long long t = 0; t < ksub; ++t) fd_block(h);

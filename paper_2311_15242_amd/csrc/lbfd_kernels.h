@@ -240,6 +240,7 @@ template <class R> struct KP {
     int gx;             // tiles along x of the node launches (64 x each)
     int gy[3];          // tiles along y for workgroups of 1, 2 and 4 rows of 64 x
     long long N;
+    long long NS;       // elements between the planes of an array with several (>= N)
     int bc[3];
     R wall_u[6][3];
     R wterm[6][QMAX];   // 6 w_i (e_i . u_w) per wall (-x,+x,-y,+y,-z,+z) and direction
