@@ -1098,6 +1098,7 @@ template <class R> struct SorOps {
     const V2<R> *w;      // node weights W = G^{n+1} + eps (psi) and X^{n+1} + eps (phi)
     V2<R> *chi;          // iterates (initial guess on entry)
     const V2<R> *rhs;
+    uint32_t bytes;      // size of each
     R hdP, hdF, om;
 };
 template <class R> __device__ __forceinline__ SorOps<R> sor_ops(const KP<R> &k, const StepArgs &)
@@ -1106,6 +1107,7 @@ template <class R> __device__ __forceinline__ SorOps<R> sor_ops(const KP<R> &k, 
     a.w = k.fld.cw2;
     a.chi = k.fld.cs2;
     a.rhs = k.fld.rhs2;
+    a.bytes = 2u * k.hn * (uint32_t)sizeof(V2<R>);
     a.hdP = R(0.5) * k.Ds;
     a.hdF = R(0.5) * k.Db;
     a.om = k.omega;
@@ -1160,9 +1162,8 @@ __device__ __forceinline__ void sor_node(const SorOps<typename P::R> &a, const S
     // diag = W_n + sum_f w_f, off = sum_f w_f chi_f over the faces present (a wall
     // face carries no flux), w_f = (Dc/2) (W_n + W_f)/2, for both systems at once.
     // FP32: each face's pairs are loaded as it is accumulated; FP64 (16-byte pairs):
-    // all faces are loaded first (measured faster in each mode; same arithmetic), but not
-    // in the persistent solve, whose registers would then allow half the wavefronts.
-    const auto chi = [&](uint32_t j) { return DEV ? ld_dev((const V2<R> *)a.chi, j) : ld((const V2<R> *)a.chi, j); };
+    // all faces are loaded first (measured faster in each mode; same arithmetic).
+    const auto chi = [&](uint32_t j) { return DEV ? ld_dev((const V2<R> *)a.chi, a.bytes, j) : ld((const V2<R> *)a.chi, j); };
     const V2<R> Wn = ld(a.w, r.n), c0 = chi(r.n), rhs = ld(a.rhs, r.n);
     R dP = Wn.x, oP = 0, dF = Wn.y, oF = 0;
     const auto face = [&](const V2<R> &Wf, const V2<R> &cf) {
@@ -1172,7 +1173,7 @@ __device__ __forceinline__ void sor_node(const SorOps<typename P::R> &a, const S
         dF += wF;
         oF += wF * cf.y;
     };
-    if constexpr (sizeof(R) == 8 && !DEV) {
+    if constexpr (sizeof(R) == 8) {
         V2<R> Wf[NF], cf[NF];
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
@@ -1200,7 +1201,7 @@ __device__ __forceinline__ void sor_node(const SorOps<typename P::R> &a, const S
         bloc[1] = fmax(bloc[1], fabs(rhs.y));
         v.y = (R(1) - a.om) * c0.y + a.om * (rhs.y + oF) / dF;
     }
-    if constexpr (DEV) st_dev(a.chi, r.n, v);
+    if constexpr (DEV) st_dev(a.chi, a.bytes, r.n, v);
     else st(a.chi, r.n, v);
 }
 
@@ -1247,7 +1248,7 @@ template <int LAT, class P> struct SorRow {
         if (!live) return;
         V2<R> cf[NF];
 #pragma unroll
-        for (int f = 0; f < NF; ++f) cf[f] = ld_dev((const V2<R> *)a.chi, q[f]);
+        for (int f = 0; f < NF; ++f) cf[f] = ld_dev((const V2<R> *)a.chi, a.bytes, q[f]);
         R oP = 0, oF = 0;
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
@@ -1264,7 +1265,7 @@ template <int LAT, class P> struct SorRow {
             bloc[1] = fmax(bloc[1], fabs(rhs.y));
             c.y = (R(1) - a.om) * c.y + a.om * (rhs.y + oF) / d.y;
         }
-        st_dev(a.chi, n, c);
+        st_dev(a.chi, a.bytes, n, c);
     }
 };
 
@@ -1684,7 +1685,7 @@ __device__ __forceinline__ void sor_sweeps(const KP<typename P::R> &k, const Ste
 // near: only the workgroups of one residue mod 8 take part. The hardware deals workgroups to
 // the eight XCDs in turn, so these share an L2.
 template <int LAT, class P, bool SEAM, bool ROWS>
-__global__ __launch_bounds__(REST_T, ROWS ? 2 : 4) void k_sor_rest(KP<typename P::R> k, int first, int nsw, int near)
+__global__ __launch_bounds__(REST_T, 2) void k_sor_rest(KP<typename P::R> k, int first, int nsw, int near)
 {
     __shared__ SorShared sh;
     if (near && (blockIdx.x & 7u) != 0u) return;
@@ -3195,10 +3196,10 @@ template <int LAT, class P> struct Impl {
 // persistent launch replaces them. Where each of its workgroups has one tile of a colour
 // (up to one workgroup per compute unit), it also takes the sweeps that do work, with the
 // rows in registers: a phase is 2.5 us on one XCD and 4 us on all of them against a launch of
-// 4.5 us (four sweeps of the 128 x 128 drop: 29 us near, 34 us on all XCDs, 43 us as three
+// 4.5 us (four sweeps of the 128 x 128 drop: 25 us near, some 30 us on all XCDs, 43 us as three
 // sweeps of launches and the rest; 512 x 256 FP32: 27 against 33 us). With more tiles than
-// that a launch over the whole chip is faster than a phase (105^3 FP64: 18 against some
-// 30 us; 96^3 FP32: three sweeps 72 against 87 us), so the first three sweeps, as many as
+// that a launch over the whole chip is faster than a phase (105^3 FP64: 15 against some
+// 22 us; 96^3 FP32: three sweeps 72 against 87 us), so the first three sweeps, as many as
 // most steps need, are launches.
 struct RestShape {
     int lead, wgs;
