@@ -11,9 +11,9 @@ reductions keep a fixed shape):
   workgroup count and occupancy;
 * ``sor_wg_per_cu``: the persistent grid of the SOR half-sweeps, in workgroups
   of 256 per compute unit;
-* ``sor_narrow``: the grid of sweeps past the third, which mostly find both
-  systems converged and return (in a batch: which run over the instances
-  still converging).
+* ``sor_narrow``: the most workgroups of the one launch that runs the sweeps
+  past the third (grids of more than one tile of 512 same-colour nodes per
+  compute unit; a batch does not use it).
 
 Each candidate is timed over whole steps with HIP events on the solver's
 stream (median of several timed regions); the fastest is stored per workload
