@@ -366,7 +366,7 @@ __global__ __launch_bounds__(256, (zm_per_cu<CIN>())) void k_conv_fwd_zm(
 // Bound: LDS reads and the matrix cores alike (an input fragment a matrix instruction). The
 // kernels before it read those fragments from global memory, 64 bytes from lane to lane:
 // 8 tiles of 40^3, 32 -> 32 channels 92 -> 42 us, 32 -> 7 51 -> 35, 6 -> 32 55 -> 32, input
-// gradient 119 -> 69; a 24^3 grid 30 -> 9 us a layer.
+// gradient 119 -> 49 (66 with its mask read where it is applied); a 24^3 grid 30 -> 9 us a layer.
 enum { FWD = 0, LAST = 1, DGRAD = 2 };
 constexpr int ROWS_NODES = 1000;   // staged nodes of a unit at most (two buffers fill the LDS)
 template <int CIN, int KIND>
@@ -426,12 +426,19 @@ __global__ __launch_bounds__(256, 1) void k_conv_rows(const u16 *__restrict__ in
         constexpr int NT = decltype(NTC)::value;
         const u16 *base[NT];
         f32x16 acc[NT];
+        // the mask's words are fetched before the products that they are applied to: with one
+        // wavefront per SIMD nothing else hides their latency
+        [[maybe_unused]] uint2 mk[NT][4];
 #pragma unroll
         for (int i = 0; i < NT; ++i) {
             const int j = min(32 * (t + i) + mr, n - 1), yy = j / Wo;
             base[i] = s + (yy * SW + (j - yy * Wo)) * CP + kg * 8;
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][e] = 0.0f;
+            if constexpr (KIND == DGRAD)
+#pragma unroll
+                for (int h = 0; h < 4; ++h)
+                    mk[i][h] = *(const uint2 *)&mask[(m0 + min(32 * (t + i) + 8 * h + 4 * kg + (lane & 3), n - 1)) * CO + (mr & ~3)];
         }
 #pragma unroll
         for (int ap = 0; ap < 9; ++ap) {
@@ -473,7 +480,7 @@ __global__ __launch_bounds__(256, 1) void k_conv_rows(const u16 *__restrict__ in
                     const long long at = (m0 + j) * CO + (mr & ~3);
                     if constexpr (KIND == DGRAD) {
                         // x > 0 for a ReLU output: its bits are not zero and its sign is clear
-                        const uint2 x = *(const uint2 *)&mask[at];
+                        const uint2 x = mk[i][h];
                         const auto keep = [](uint32_t g, uint32_t w) {
                             const uint32_t lo = w & 0xffffu, hi = w >> 16;
                             return g & ((lo - 1u < 0x7fffu ? 0xffffu : 0u) | (hi - 1u < 0x7fffu ? 0xffff0000u : 0u));
