@@ -547,8 +547,9 @@ inline int rows_per_unit(int B, int Do, int Ho, int Wo, int cus)
 // every other sixteen nodes (w / 4); a persistent workgroup adds them to dw with atomics once.
 //
 // Bound: the latency of staging a unit (some 3 us against 1 us of products) and, at the end, the
-// atomics (22 of 60 us on 8 tiles of 40^3). The kernel before it read x and dy once per tap and
-// transposed them by 2-byte LDS stores: 112 -> 60 us with 32 input channels, 112 -> 48 with 16.
+// atomics (some 14 of 53 us on 8 tiles of 40^3; 22 of 60 with all workgroups adding in the same
+// order). The kernel before it read x and dy once per tap and transposed them by 2-byte LDS
+// stores: 112 -> 53 us with 32 input channels, 112 -> 48 with 16.
 constexpr int WG_T = 512;
 constexpr int WG_TAPS = 7;       // taps of a wavefront
 constexpr int WG_NODES = 1000;   // staged nodes (x and dy) of a unit at most
@@ -687,19 +688,23 @@ __global__ __launch_bounds__(WG_T, 2) void k_conv_wgrad(const u16 *__restrict__ 
 #pragma unroll
             for (int e = 0; e < 16; ++e) sums[((set * WG_TAPS + j) * 16 + e) * 64 + lane] = acc[j][e];
     __syncthreads();
-    if (half) return;
+    if (!half)
 #pragma unroll
-    for (int j = 0; j < WG_TAPS; ++j) {
-        const int t = set * WG_TAPS + j;
+        for (int j = 0; j < WG_TAPS; ++j)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const float s = acc[j][e] + sums[((set * WG_TAPS + j) * 16 + e) * 64 + lane];
-            const int i = acc_row(e, kg);
-            if (t == 27) {
-                if (i == 0 && s != 0.0f) atomicAdd(&db[mr], s);
-            } else if (i < CIN && s != 0.0f) {
-                atomicAdd(&dw[((long long)t * CIN + i) * CO + mr], s);
-            }
+            for (int e = 0; e < 16; ++e) sums[((set * WG_TAPS + j) * 16 + e) * 64 + lane] += acc[j][e];
+    __syncthreads();
+    // every workgroup starts at another place: in step they would all add to the same lines
+    constexpr int G = 4 * WG_TAPS * 16;
+    const int rot = (int)(blockIdx.x * (unsigned)G / gridDim.x);
+    for (int q = wave; q < G; q += WG_T / 64) {
+        const int g = q + rot < G ? q + rot : q + rot - G, t = g >> 4, i = acc_row(g & 15, kg);
+        const float s = sums[g * 64 + lane];
+        if (s == 0.0f) continue;
+        if (t == 27) {
+            if (i == 0) atomicAdd(&db[mr], s);
+        } else if (i < CIN) {
+            atomicAdd(&dw[((long long)t * CIN + i) * CO + mr], s);
         }
     }
 }
