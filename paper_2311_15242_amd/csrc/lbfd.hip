@@ -2417,11 +2417,12 @@ struct Layout {
 // Elements between the planes of an array with several (populations, macroscopic fields,
 // vectors). On grids with powers of two in their extents planes of N elements start at
 // the same place of the memory channels' interleave, so the up to 33 streams of a kernel
-// visit the same channels at the same time; an odd multiple of 128 elements (a line of 256
-// bytes in two-byte planes) between them ends that. 256^3 FP32: collide 920 -> 855 us;
-// 128 x 128 x 384 with BF16 populations: 216 -> 206 us. Grids with other extents
+// visit the same channels at the same time; 576 elements between them (nine lines of 256
+// bytes in four-byte planes, four and a half in two-byte ones) end that. 256^3 FP32: collide
+// 923 -> 859 us; 128 x 128 x 384 with BF16 populations: collide 216 -> 188, macro 199 -> 189 us
+// (2,176 elements: 854, 206 and 196 us; 128: 924, 208 and 197). Grids with other extents
 // (320 x 240 x 200: 718 us) and the other kernels are the same with and without it.
-long long plane_stride(long long N) { return (N + 127) / 128 * 128 + 17 * 128; }
+long long plane_stride(long long N) { return (N + 63) / 64 * 64 + 576; }
 
 Layout layout(const lbfd_params *p)
 {
