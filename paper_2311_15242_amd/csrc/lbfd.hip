@@ -943,26 +943,34 @@ __global__ __launch_bounds__(256) void kb_macro(const KP<typename P::R> *tab, co
 
 // ============================================================== finite differences
 
-// WENO3 one-sided difference of eqs 26-27 at node i, from the side that the nodes a, b (two
-// and one before it) lie on: D- with a = Psi_{i-2}, b = Psi_{i-1}, c = Psi_{i+1}, and -D+ with
-// the line reversed. With A = eps + (D+D- at b)^2 and B = eps + (D+D- at i)^2 the weight
-// 1/(1 + 2 r^2) is B^2/(B^2 + 2A^2) (all terms >= eps^2).
-template <class R> __device__ __forceinline__ R weno_side(R a, R b, R o, R c, R eps)
+// Upwind mix H+ D- + H- D+ of the WENO3 one-sided differences of eqs 26-27 at the centre of a
+// 5-point line P[0..4] = Psi at i-2..i+2. With A = eps + (D+D- at i-1)^2, B = eps + (D+D- at i)^2,
+// C = eps + (D+D- at i+1)^2 the weights 1/(1 + 2 r^2) are B^2/(B^2 + 2A^2) and
+// B^2/(B^2 + 2C^2); both come from one reciprocal of the product of their denominators (all
+// terms >= eps^2). H+ = u+/|u| and H- = |u-|/|u| are exactly 1 or 0 away from the +-upwind_eps
+// band, so a node forms the difference of the side the flow comes from (fwd: D-) with the
+// weight it has in the pair, and in the band both (BRANCH: where a wavefront has such a node).
+template <bool BRANCH, class R> __device__ __forceinline__ R weno_upwind(const R *P, R eps, bool fwd, bool band)
 {
-    const R d_2 = b - a, d_1 = o - b, d0 = c - o;
-    const R dd_1 = o - R(2) * b + a, dd0 = c - R(2) * o + b;
-    const R A = eps + dd_1 * dd_1, B = eps + dd0 * dd0, B2 = B * B;
-    const R w = B2 * fast_rcp(B2 + R(2) * A * A);
-    return R(0.5) * ((d_1 + d0) - w * (d_2 - R(2) * d_1 + d0));
+    const R d_2 = P[1] - P[0], d_1 = P[2] - P[1], d0 = P[3] - P[2], d1 = P[4] - P[3];
+    const R dd_1 = P[2] - R(2) * P[1] + P[0], dd0 = P[3] - R(2) * P[2] + P[1], dd1 = P[4] - R(2) * P[3] + P[2];
+    const R A = eps + dd_1 * dd_1, B = eps + dd0 * dd0, C = eps + dd1 * dd1;
+    const R B2 = B * B, den_m = B2 + R(2) * A * A, den_p = B2 + R(2) * C * C;
+    const R inv = fast_rcp(den_m * den_p);
+    const R tm = d_2 - R(2) * d_1 + d0, tp = d1 - R(2) * d0 + d_1;
+    const R w = B2 * (fwd ? den_p : den_m) * inv;
+    const R one = R(0.5) * ((d_1 + d0) - w * (fwd ? tm : tp));
+    if (BRANCH && __ballot(band) == 0ull) return one;
+    const R v = B2 * (fwd ? den_m : den_p) * inv;
+    const R other = R(0.5) * ((d_1 + d0) - v * (fwd ? tp : tm));
+    return band ? R(0.5) * one + R(0.5) * other : one;
 }
 
 // The cross of a 64 x TY node tile (one plane) in LDS, two nodes wide along x and y: psi, W =
-// |grad rhoN| + eps, phi and X = 1 - rhoN + eps in one cell, u_x and u_y. Cell (2 + x, 2 + y).
-// The kernel is bound by its instructions as much as by its 68 bytes a node (FP32): each node's
-// products are used on every line through it, so W and X are formed once, and a line's nodes
-// along x and y are one LDS read where they were four gathers. Together with the one-sided
-// differences below: 128 x 128 x 384 FP32 arithmetic 159 -> 121 us, 105^3 FP64 86 -> 68 us,
-// 64 columns of 1e5 nodes 139 -> 129 us (LDS alone: 154, 74 and 132 us).
+// |grad rhoN| + eps, phi and X = 1 - rhoN + eps in one cell, and u_x and u_y times the lazy scale
+// s of the stored psi, phi. Cell (2 + x, 2 + y). Each node's products are used on every line
+// through it, so W and X are formed once, and a line's nodes along x and y are one LDS read where
+// they were four gathers.
 template <class R, int TY> struct FdCross {
     static constexpr int CX = BX + 4, CY = TY + 4;
     V4<R> c[CY * CX];
@@ -970,7 +978,7 @@ template <class R, int TY> struct FdCross {
 };
 template <int LAT, int TY, class R>
 __device__ __forceinline__ void stage_cross(const KP<R> &k, int tile, const R *psi, const R *phi, const R *G, const R *rN,
-                                            FdCross<R, TY> &sh)
+                                            R s, FdCross<R, TY> &sh)
 {
     using C = FdCross<R, TY>;
     constexpr int RPW = (C::CY + TY - 1) / TY;   // rows per wavefront
@@ -1004,15 +1012,24 @@ __device__ __forceinline__ void stage_cross(const KP<R> &k, int tile, const R *p
         if (row >= C::CY) continue;
         const bool mid = row >= 2 && row < 2 + TY;
         sh.c[row * C::CX + 2 + lane] = cell(v0[i]);
-        sh.uy[row * BX + lane] = b0[i];
+        sh.uy[row * BX + lane] = s * b0[i];
         if (!mid) continue;
-        sh.ux[(row - 2) * C::CX + 2 + lane] = a0[i];
+        sh.ux[(row - 2) * C::CX + 2 + lane] = s * a0[i];
         if (lane >= 4) continue;
         sh.c[row * C::CX + c1] = cell(v1[i]);
-        sh.ux[(row - 2) * C::CX + c1] = a1[i];
+        sh.ux[(row - 2) * C::CX + c1] = s * a1[i];
     }
 }
 
+// Bound by instructions as much as by its 68 bytes a node (FP32), and by the wavefronts in
+// flight: in 3-D and in FP64 an axis is finished before the next one's loads are issued (FP32
+// 59 registers instead of 85: eight wavefronts per SIMD instead of five), and a difference of
+// the side the flow does not come from is branched over; in 2-D FP32 (62 registers as it
+// is) both cost more than they save (2048^2: 75 us against 71). With all gathers from memory and
+// both differences at every node, and now: 128 x 128 x 384 in 16-bit storage 168 -> 139 us, 105^3
+// FP64 88 -> 73, 256^3 FP32 451 -> 385, 2048^2 FP64 199 -> 150. A difference with a weight of its
+// own (no denominator of the other side) takes 127, 66, 350 and 135 us, but rounds otherwise,
+// and 16-bit populations carry a last bit to 2e-4 of the colour function in some hundred steps.
 template <int LAT, class P, int TY>
 __device__ __forceinline__ void fd_body(const KP<typename P::R> &k, int tile, const StepArgs &sa)
 {
@@ -1020,84 +1037,69 @@ __device__ __forceinline__ void fd_body(const KP<typename P::R> &k, int tile, co
     using L = Lat<LAT>;
     using C = FdCross<R, TY>;
     constexpr int D = L::D;
+    constexpr bool APART = D == 3 || sizeof(R) == 8;   // axes one after the other
     Node nd = node_at(k, tile);
     __shared__ C sh;
-    stage_cross<LAT, TY, R>(k, tile, k.fld.psi[sa.pc], k.fld.phi[sa.pc], k.fld.G[sa.lev], k.fld.mac[sa.lev] + 2 * k.NS, sh);
+    const R s = (R)k.fld.sc->scale;
+    stage_cross<LAT, TY, R>(k, tile, k.fld.psi[sa.pc], k.fld.phi[sa.pc], k.fld.G[sa.lev], k.fld.mac[sa.lev] + 2 * k.NS, s, sh);
     __syncthreads();
     if (!nd.ok) return;
     const int x = nd.x, y = nd.y, z = nd.z;
     const long long N = k.NS;   // between planes
     const uint32_t n = node_index(k, nd);
-    const R s = (R)k.fld.sc->scale;
     const R *psiA = k.fld.psi[sa.pc], *phiA = k.fld.phi[sa.pc];
     const R *G0 = k.fld.G[sa.lev];
     const R *rN0 = k.fld.mac[sa.lev] + 2 * N;
     const R *uv = k.fld.u;
     const Nbhd nb = make_nbhd(k, x, y, z);
-    // Convection: H+ = u+/|u| and H- = |u-|/|u| of the upwind mix H+ D- + H- D+ are exactly 1 or
-    // 0 away from the +-upwind_eps band, so a node takes four nodes of each axis and one
-    // difference, of the side the flow comes from; in the band it adds the other one.
-    const int cs = (int)(threadIdx.x + 2) + C::CX * (int)(threadIdx.y + 2);
+    const int tx = (int)threadIdx.x, ty = (int)threadIdx.y;
+    const int cs = tx + 2 + C::CX * (ty + 2);
     const V4<R> own = sh.c[cs];
-    V4<R> cm[D], cp[D];   // face neighbours
-    R divP = 0, divF = 0;
-#pragma unroll
-    for (int a = 0; a < D; ++a) {
-        // node o of the axis: along x and y from LDS, along z from memory
-        const auto at = [&](int o) -> V4<R> {
-            if (a < 2) return sh.c[cs + (a == 0 ? o : C::CX * o)];
-            const uint32_t q = n + (uint32_t)(o == -2 ? nb.d[2][0] : o == -1 ? nb.d[2][1] : o == 1 ? nb.d[2][2] : nb.d[2][3]);
-            return V4<R>{ld(psiA, q), ld(G0, q) + k.fd_eps, ld(phiA, q), (R(1) - ld(rN0, q)) + k.fd_eps};
-        };
-        const auto vel = [&](int o) -> R {
-            if (a == 0) return sh.ux[(int)(threadIdx.x + 2) + C::CX * (int)threadIdx.y + o];
-            if (a == 1) return sh.uy[(int)threadIdx.x + BX * ((int)(threadIdx.y + 2) + o)];
-            return ld(uv + 2 * N, n + (uint32_t)(o == -2 ? nb.d[2][0] : o == -1 ? nb.d[2][1] : o == 1 ? nb.d[2][2] : nb.d[2][3]));
-        };
-        // the lazy scale of the stored psi, phi and the mirror sign ride on u_a
-        const auto sgn = [&](int o) { return ((nb.mir >> (a * 4 + slot_of(o))) & 1u) ? R(-1) : R(1); };
-        const R ua = a == 0   ? sh.ux[(int)(threadIdx.x + 2) + C::CX * (int)threadIdx.y]
-                     : a == 1 ? sh.uy[(int)threadIdx.x + BX * (int)(threadIdx.y + 2)]
-                              : ld(uv + 2 * N, n);
-        const R su = s * ua, sm = sgn(-1) * (s * vel(-1)), sp = sgn(1) * (s * vel(1));
-        cm[a] = at(-1);
-        cp[a] = at(1);
-        const R oP = (own.x * own.y) * su, mP = (cm[a].x * cm[a].y) * sm, pP = (cp[a].x * cp[a].y) * sp;
-        const R oF = (own.z * own.w) * su, mF = (cm[a].z * cm[a].w) * sm, pF = (cp[a].z * cp[a].w) * sp;
-        const auto side = [&](bool fwd, R h) {   // fwd: D-
-            const int o = fwd ? -2 : 2;
-            const V4<R> e = at(o);
-            const R se = sgn(o) * (s * vel(o));
-            const R hs = fwd ? h : -h;
-            divP += hs * weno_side((e.x * e.y) * se, fwd ? mP : pP, oP, fwd ? pP : mP, k.weno_eps);
-            divF += hs * weno_side((e.z * e.w) * se, fwd ? mF : pF, oF, fwd ? pF : mF, k.weno_eps);
-        };
-        const bool band = fabs(ua) <= k.upwind_eps, fwd = ua > R(0);
-        side(fwd, band ? R(0.5) : R(1));
-        if (band) side(!fwd, R(0.5));
-    }
-    const R psi = s * own.x, phi = s * own.z;
     // weights of eqs 20-21 with the background support
     const R Gn = own.y, Xn = own.w;
+    R divP = 0, divF = 0;
+    // diffusion operator of eq 28 with half-point weights, as printed (the neighbour sums
+    // over the stored psi, phi, scaled once)
+    R swP = 0, swcP = 0, swF = 0, swcF = 0;
+    const auto face = [&](const V4<R> &c) {
+        const R wP = R(0.5) * (Gn + c.y), wF = R(0.5) * (Xn + c.w);
+        swcP += wP * c.x;
+        swP += wP;
+        swcF += wF * c.z;
+        swF += wF;
+    };
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+        R Pp[5], Pf[5];
+#pragma unroll
+        for (int o = -2; o <= 2; ++o) {
+            // psi, W, phi, X and s u_a of the node: along x and y from LDS, along z from memory
+            const uint32_t q = o == 0 ? n : n + (uint32_t)nb.d[a][slot_of(o)];
+            V4<R> c;
+            R us;
+            if (o == 0) c = own;
+            else if (a < 2) c = sh.c[cs + (a == 0 ? o : C::CX * o)];
+            else c = V4<R>{ld(psiA, q), ld(G0, q) + k.fd_eps, ld(phiA, q), (R(1) - ld(rN0, q)) + k.fd_eps};
+            if (a == 0) us = sh.ux[tx + 2 + o + C::CX * ty];
+            else if (a == 1) us = sh.uy[tx + BX * (ty + 2 + o)];
+            else us = s * ld(uv + 2 * N, q);
+            if (o == -1 || o == 1) face(c);
+            const R sg = (o != 0 && ((nb.mir >> (a * 4 + slot_of(o))) & 1u)) ? R(-1) : R(1);
+            const R su = sg * us;   // the mirror sign rides on u_a too
+            Pp[o + 2] = (c.x * c.y) * su;
+            Pf[o + 2] = (c.z * c.w) * su;
+        }
+        const R ua = ld(uv + a * N, n);
+        const bool band = fabs(ua) <= k.upwind_eps, fwd = ua > R(0);
+        divP += weno_upwind<APART>(Pp, k.weno_eps, fwd, band);
+        divF += weno_upwind<APART>(Pf, k.weno_eps, fwd, band);
+        if constexpr (APART) __builtin_amdgcn_sched_barrier(0);
+    }
+    const R psi = s * own.x, phi = s * own.z;
     const R jj = k.source_mode == 1 ? k.ra * k.psi_inf * phi : k.ra * phi * (k.psi_inf - psi) - k.rd * psi;
     const R Sn = -divP + Gn * jj, Bn = -divF - Gn * jj;
     const R eS = sa.step == 0 ? Sn : R(1.5) * Sn - R(0.5) * ld(k.fld.Sp, n);
     const R eB = sa.step == 0 ? Bn : R(1.5) * Bn - R(0.5) * ld(k.fld.Bp, n);
-    // diffusion operator of eq 28 with half-point weights, as printed (the neighbour sums
-    // over the stored psi, phi, scaled once)
-    R swP = 0, swcP = 0, swF = 0, swcF = 0;
-#pragma unroll
-    for (int a = 0; a < D; ++a)
-#pragma unroll
-        for (int o = -1; o <= 1; o += 2) {
-            const V4<R> c = o < 0 ? cm[a] : cp[a];
-            R wP = R(0.5) * (Gn + c.y);
-            R wF = R(0.5) * (Xn + c.w);
-            swcP += wP * c.x;
-            swP += wP;
-            swcF += wF * c.z;
-            swF += wF;
-        }
     const R rhP = Gn * psi + R(0.5) * k.Ds * (s * swcP - swP * psi) + eS;
     const R rhF = Xn * phi + R(0.5) * k.Db * (s * swcF - swF * phi) + eB;
     st(k.fld.Sp, n, Sn);
