@@ -1610,14 +1610,16 @@ template <class R> __device__ __forceinline__ uint32_t seam_nodes(const KP<R> &k
            (k.seam & 4 ? (uint32_t)(k.nx * k.ny) : 0u);
 }
 
-// The last seam levels (both in 2-D, where they are a row, a column and their corner; the edges
-// and the corner in 3-D) by one workgroup, with its own barrier between their half-sweeps.
+// The seam levels from lv0 on by one workgroup, with its own barrier between their half-sweeps.
+// In 2-D level 1 is a row and a column and level 2 their corner; in 3-D level 2 is the
+// edges and level 3 the corner (level 1, the planes, is never taken here).
 template <int LAT, class P, int NT, bool DEV>
-__device__ __forceinline__ void sor_seam_tail(const KP<typename P::R> &k, const SorOps<typename P::R> &a,
+__device__ __forceinline__ void sor_seam_tail(const KP<typename P::R> &k, const SorOps<typename P::R> &a, int lv0,
                                               const bool *conv, typename P::R *rloc, typename P::R *bloc)
 {
+    constexpr int D = Lat<LAT>::D;
     const int levels = __builtin_popcount((unsigned)k.seam);
-    if constexpr (Lat<LAT>::D == 2) {
+    if (D == 2 && lv0 == 1) {
         const uint32_t S = seam_nodes(k);
         for (int h = 2; h < 2 + 2 * levels; ++h) {
             for (uint32_t t = threadIdx.x; t < S; t += NT)
@@ -1625,30 +1627,36 @@ __device__ __forceinline__ void sor_seam_tail(const KP<typename P::R> &k, const 
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
         }
-    } else {
-        // the edges along z, y and x (of the seam axis pairs xy, xz and yz) one after another,
-        // the corner from the first of them
-        const uint32_t ez = (k.seam & 3) == 3 ? (uint32_t)k.nz : 0u, ey = (k.seam & 5) == 5 ? (uint32_t)k.ny : 0u,
-                       ex = (k.seam & 6) == 6 ? (uint32_t)k.nx : 0u;
-        for (int h = 4; h < 2 + 2 * levels; ++h) {
-            for (uint32_t t = threadIdx.x; t < ez + ey + ex; t += NT) {
-                int x = k.nx - 1, y = k.ny - 1, z = k.nz - 1;
-                bool corner = levels == 3;
-                if (t < ez) corner = corner && (int)t == z, z = (int)t;
-                else if (t < ez + ey) corner = corner && (int)(t - ez) == y, y = (int)(t - ez);
-                else corner = corner && (int)(t - ez - ey) == x, x = (int)(t - ez - ey);
-                if ((h >> 1) != (corner ? 3 : 2) || (corner && t >= ez) || ((x + y + z) & 1) != (h & 1)) continue;
-                const uint32_t L = (uint32_t)(x >> 1) + k.hx * (uint32_t)(y + k.ny * z);
-                sor_node<LAT, P, DEV>(a, sor_idx<LAT>(k, L, x, y, z, h & 1), conv, rloc, bloc);
+        return;
+    }
+    // the edges along z, y and x (of the seam axis pairs xy, xz and yz) one after another,
+    // the corner from the first of them; from the corner's level on one node
+    const bool edges = D == 3 && lv0 == 2;
+    const uint32_t ez = !edges ? (levels == D ? 1u : 0u) : (k.seam & 3) == 3 ? (uint32_t)k.nz : 0u,
+                   ey = edges && (k.seam & 5) == 5 ? (uint32_t)k.ny : 0u,
+                   ex = edges && (k.seam & 6) == 6 ? (uint32_t)k.nx : 0u;
+    for (int h = 2 * lv0; h < 2 + 2 * levels; ++h) {
+        for (uint32_t t = threadIdx.x; t < ez + ey + ex; t += NT) {
+            int x = k.nx - 1, y = k.ny - 1, z = k.nz - 1;
+            bool corner = levels == D;
+            if (t < ez) {
+                if (edges) corner = corner && (int)t == z, z = (int)t;
+            } else if (t < ez + ey) {
+                corner = corner && (int)(t - ez) == y, y = (int)(t - ez);
+            } else {
+                corner = corner && (int)(t - ez - ey) == x, x = (int)(t - ez - ey);
             }
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();
+            if ((h >> 1) != (corner ? D : 2) || (corner && t >= ez) || ((x + y + z) & 1) != (h & 1)) continue;
+            const uint32_t L = (uint32_t)(x >> 1) + k.hx * (uint32_t)(y + k.ny * z);
+            sor_node<LAT, P, DEV>(a, sor_idx<LAT>(k, L, x, y, z, h & 1), conv, rloc, bloc);
         }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
     }
 }
 
 // One phase of the persistent solve over this member's share of its rows, then the meeting: the
-// half-sweep `color` of sweep s (lv 0), of seam level lv, or (lv < 0) the last seam levels.
+// half-sweep `color` of sweep s (lv 0), of seam level lv, or (lv < 0) the seam levels from -lv on.
 template <int LAT, class P, bool SEAM>
 __device__ __forceinline__ uint32_t sor_phase(const KP<typename P::R> &k, const SorOps<typename P::R> &a, SorGroup &g,
                                               int s, int color, int lv, uint32_t open, double lim0, double lim1,
@@ -1669,7 +1677,7 @@ __device__ __forceinline__ uint32_t sor_phase(const KP<typename P::R> &k, const 
             sor_seam_node<LAT, P, true>(k, a, t, lv, color, conv, rloc, bloc);
     } else if (g.rank == 0u) {
         // with seam classes the test is over a whole sweep: either colour's slot will do
-        sor_seam_tail<LAT, P, REST_T, true>(k, a, conv, rloc, bloc);
+        sor_seam_tail<LAT, P, REST_T, true>(k, a, -lv, conv, rloc, bloc);
     }
     return sor_meet(k, g, s, color, open, rloc, bloc, lim0, lim1, sh);
 }
@@ -1690,11 +1698,12 @@ __device__ __forceinline__ uint32_t sor_open(const KP<typename P::R> &k, int fir
     return open;
 }
 
-// Sweeps first .. nsw - 1 of one instance by the group, with `open` systems left to solve. ROWS:
+// Sweeps first .. nsw - 1 of one instance by the group, with `open` systems left to solve, its
+// seam levels from lv0 on by one workgroup. ROWS:
 // a member has one tile of each colour at most, and keeps its rows in registers.
 template <int LAT, class P, bool SEAM, bool ROWS>
 __device__ __forceinline__ void sor_sweeps_as(const KP<typename P::R> &k, const StepArgs &sa, SorGroup &g, int first,
-                                              int nsw, uint32_t open, SorShared &sh)
+                                              int nsw, int lv0, uint32_t open, SorShared &sh)
 {
     using R = typename P::R;
     const SorOps<R> a = sor_ops(k, sa);
@@ -1739,9 +1748,9 @@ __device__ __forceinline__ void sor_sweeps_as(const KP<typename P::R> &k, const 
         }
         left |= phase(s, 1, 0, lim0, lim1);
         if constexpr (SEAM) {
-            constexpr int LV0 = Lat<LAT>::D - 1;   // first of the levels that one workgroup takes
-            for (int h = 2; h < 2 * LV0; ++h) left |= phase(s, h & 1, h >> 1, lim0, lim1);
-            if (__builtin_popcount((unsigned)k.seam) >= LV0) left |= phase(s, 0, -1, lim0, lim1);
+            const int levels = __builtin_popcount((unsigned)k.seam);
+            for (int h = 2; h < 2 * min(lv0, levels + 1); ++h) left |= phase(s, h & 1, h >> 1, lim0, lim1);
+            if (levels >= lv0) left |= phase(s, 0, -lv0, lim0, lim1);
         }
         if (!k.sor_exact && s > 0) {
             open &= left;
@@ -1751,20 +1760,21 @@ __device__ __forceinline__ void sor_sweeps_as(const KP<typename P::R> &k, const 
 }
 template <int LAT, class P, bool SEAM, bool ROWS>
 __device__ __forceinline__ void sor_sweeps(const KP<typename P::R> &k, const StepArgs &sa, SorGroup &g, int first,
-                                           int nsw, uint32_t open, SorShared &sh)
+                                           int nsw, int lv0, uint32_t open, SorShared &sh)
 {
     if constexpr (ROWS)
         if (k.hn <= g.members * REST_T) {
-            sor_sweeps_as<LAT, P, SEAM, true>(k, sa, g, first, nsw, open, sh);
+            sor_sweeps_as<LAT, P, SEAM, true>(k, sa, g, first, nsw, lv0, open, sh);
             return;
         }
-    sor_sweeps_as<LAT, P, SEAM, false>(k, sa, g, first, nsw, open, sh);
+    sor_sweeps_as<LAT, P, SEAM, false>(k, sa, g, first, nsw, lv0, open, sh);
 }
 
 // near: only the workgroups of one residue mod 8 take part. The hardware deals workgroups to
 // the eight XCDs in turn, so these share an L2.
 template <int LAT, class P, bool SEAM, bool ROWS>
-__global__ __launch_bounds__(REST_T, 2) void k_sor_rest(KP<typename P::R> k, int first, int nsw, int near)
+__global__ __launch_bounds__(REST_T, 2) void k_sor_rest(KP<typename P::R> k, int first, int nsw, int lv0,
+                                                         int near)
 {
     __shared__ SorShared sh;
     if (near && (blockIdx.x & 7u) != 0u) return;
@@ -1772,7 +1782,7 @@ __global__ __launch_bounds__(REST_T, 2) void k_sor_rest(KP<typename P::R> k, int
     if (open == 0u) return;   // the usual case after some sweeps by launches
     SorGroup g = sor_enrol(k.fld.sync, near ? gridDim.x >> 3 : gridDim.x, sh);
     if (g.members == 0u) return;
-    sor_sweeps<LAT, P, SEAM, ROWS>(k, step_args(k), g, first, nsw, open, sh);
+    sor_sweeps<LAT, P, SEAM, ROWS>(k, step_args(k), g, first, nsw, lv0, open, sh);
 }
 
 // Batch: `groups` groups of `per` workgroups (group i on the XCD i mod 8), group i solving the
@@ -1780,7 +1790,7 @@ __global__ __launch_bounds__(REST_T, 2) void k_sor_rest(KP<typename P::R> k, int
 // that XCD's L2 from phase to phase, and while one group meets another one works.
 template <int LAT, class P, bool SEAM, bool ROWS>
 __global__ __launch_bounds__(REST_T, ROWS ? 2 : 4) void kb_sor_rest(const KP<typename P::R> *tab, int ninst, StepArgs sa, int first,
-                                                     int nsw, int groups, int per)
+                                                     int nsw, int lv0, int groups, int per)
 {
     __shared__ SorShared sh;
     const int i0 = (int)(blockIdx.x >> 3) / per * 8 + (int)(blockIdx.x & 7u);
@@ -1793,13 +1803,13 @@ __global__ __launch_bounds__(REST_T, ROWS ? 2 : 4) void kb_sor_rest(const KP<typ
             g = sor_enrol(tab[i0].fld.sync, (uint32_t)per, sh);
             if (g.members == 0u) return;
         }
-        sor_sweeps<LAT, P, SEAM, ROWS>(tab[i], sa, g, first, nsw, open, sh);
+        sor_sweeps<LAT, P, SEAM, ROWS>(tab[i], sa, g, first, nsw, lv0, open, sh);
         __syncthreads();
     }
 }
 
 // One parity half-sweep of one seam level (one thread per entry of the seam index space), or
-// (level < 0, one workgroup) the last levels.
+// (level < 0, one workgroup) the levels from -level on.
 template <int LAT, class P>
 __device__ __forceinline__ void sor_seam_body(const KP<typename P::R> &k, const StepArgs &sa, uint32_t local, int level,
                                               int color, int sweep)
@@ -1810,7 +1820,7 @@ __device__ __forceinline__ void sor_seam_body(const KP<typename P::R> &k, const 
     if (conv[0] && conv[1]) return;
     R rloc[2] = {0, 0}, bloc[2] = {0, 0};
     const SorOps<R> a = sor_ops(k, sa);
-    if (level < 0) sor_seam_tail<LAT, P, 256, false>(k, a, conv, rloc, bloc);
+    if (level < 0) sor_seam_tail<LAT, P, 256, false>(k, a, -level, conv, rloc, bloc);
     else sor_seam_node<LAT, P>(k, a, local * 256u + threadIdx.x, level, color, conv, rloc, bloc);
     block_max_to_slots(conv[0] ? R(-1) : rloc[0], conv[1] ? R(-1) : rloc[1], k.fld.sorres, 2 * sweep + color);
     if (sweep == 0) block_max_to_slots(bloc[0], bloc[1], k.fld.sorres, RMAX_IDX);
@@ -1822,7 +1832,7 @@ __global__ __launch_bounds__(256) void k_sor_seam(KP<typename P::R> k, int level
 }
 
 // The same for a batch: instance i owns workgroups prefix[i] .. prefix[i+1]-1 (prefix null: one
-// workgroup, the last levels).
+// workgroup, the levels from -level on).
 template <int LAT, class P>
 __global__ __launch_bounds__(256) void kb_sor_seam(const KP<typename P::R> *tab, const int *prefix, int ninst,
                                                   StepArgs sa, int level, int color, int sweep)
@@ -2366,6 +2376,7 @@ struct lbfd_handle {
     bool rest_near;     // they all sit on one XCD
     int seam_tiles;     // workgroups over the seam index space (0: no seam classes)
     int seam_levels;    // seam levels (periodic axes of odd extent)
+    int seam_lv0;       // the first one that goes to one workgroup
     bool prof;
     unsigned prof_mask;  // kernel classes timed when profiling (bit per class)
     std::vector<ProfRec> recs;
@@ -2396,6 +2407,7 @@ struct lbfd_batch {
     int *prefix_seam;   // device: first seam workgroup of each instance (n + 1 entries)
     dim3 grid_node, grid_sor, grid_total, grid_seam;
     int seam_levels;    // most seam levels of any instance
+    int seam_lv0;       // as for a single handle, the same for every instance
     int sor_lead;       // as for a single handle, the same for every instance
     int rest_groups;    // groups of the persistent solve (each takes every rest_groups-th instance)
     int rest_wgs;       // workgroups of a group
@@ -2701,7 +2713,6 @@ static size_t field_count(const lbfd_handle *h, int field)
 
 template <int LAT, class P> struct Impl {
     using R = typename P::R;
-    static constexpr int SEAM_LV0 = Lat<LAT>::D - 1;   // seam levels from here on go to one workgroup
 
     static KP<R> &kp(lbfd_handle *h)
     {
@@ -2848,15 +2859,16 @@ template <int LAT, class P> struct Impl {
             }
             LAUNCH(KC_SOR, (k_sor<LAT, P, true>), gs, dim3(256), k, 0, s);
             LAUNCH(KC_SOR, (k_sor<LAT, P, true>), gs, dim3(256), k, 1, s);
-            for (int c = 0; c < 2 && SEAM_LV0 > 1; ++c)
-                LAUNCH(KC_SOR, (k_sor_seam<LAT, P>), dim3(h->seam_tiles), dim3(256), k, 1, c, s);
-            if (h->seam_levels >= SEAM_LV0) LAUNCH(KC_SOR, (k_sor_seam<LAT, P>), dim3(1), dim3(256), k, -1, 0, s);
+            for (int e = 2; e < 2 * std::min(h->seam_lv0, h->seam_levels + 1); ++e)
+                LAUNCH(KC_SOR, (k_sor_seam<LAT, P>), dim3(h->seam_tiles), dim3(256), k, e >> 1, e & 1, s);
+            if (h->seam_levels >= h->seam_lv0)
+                LAUNCH(KC_SOR, (k_sor_seam<LAT, P>), dim3(1), dim3(256), k, -h->seam_lv0, 0, s);
         }
         if (lead < h->sweeps_launch) {
             const dim3 gr(h->rest_near ? 8 * h->rest_wgs : h->rest_wgs);
             const int near = (int)h->rest_near;
 #define LAUNCH_REST(SEAM, ROWS) \
-    LAUNCH(KC_SOR, (k_sor_rest<LAT, P, SEAM, ROWS>), gr, dim3(REST_T), k, lead, h->sweeps_launch, near)
+    LAUNCH(KC_SOR, (k_sor_rest<LAT, P, SEAM, ROWS>), gr, dim3(REST_T), k, lead, h->sweeps_launch, h->seam_lv0, near)
             if (lead == 0 && h->seam_levels == 0) LAUNCH_REST(false, true);
             else if (lead == 0) LAUNCH_REST(true, true);
             else if (h->seam_levels == 0) LAUNCH_REST(false, false);
@@ -3003,16 +3015,18 @@ template <int LAT, class P> struct Impl {
                             LAUNCH(KC_SOR, (kb_sor<LAT, P, true>), b->grid_sor, dim3(256), tab, b->prefix_sor, n, sa, c, s);
                     }
                     if (b->seam_levels == 0) continue;
-                    for (int c = 0; c < 2 && SEAM_LV0 > 1; ++c)
-                        LAUNCH(KC_SOR, (kb_sor_seam<LAT, P>), b->grid_seam, dim3(256), tab, b->prefix_seam, n, sa, 1, c, s);
-                    if (b->seam_levels >= SEAM_LV0)
-                        LAUNCH(KC_SOR, (kb_sor_seam<LAT, P>), dim3(n), dim3(256), tab, (const int *)nullptr, n, sa, -1, 0, s);
+                    for (int e = 2; e < 2 * std::min(b->seam_lv0, b->seam_levels + 1); ++e)
+                        LAUNCH(KC_SOR, (kb_sor_seam<LAT, P>), b->grid_seam, dim3(256), tab, b->prefix_seam, n, sa, e >> 1,
+                               e & 1, s);
+                    if (b->seam_levels >= b->seam_lv0)
+                        LAUNCH(KC_SOR, (kb_sor_seam<LAT, P>), dim3(n), dim3(256), tab, (const int *)nullptr, n, sa,
+                               -b->seam_lv0, 0, s);
                 }
                 if (lead < h->sweeps_launch) {
                     const dim3 gr((unsigned)(8 * ((b->rest_groups + 7) / 8) * b->rest_wgs));
 #define LAUNCH_REST(SEAM, ROWS)                                                                          \
     LAUNCH(KC_SOR, (kb_sor_rest<LAT, P, SEAM, ROWS>), gr, dim3(REST_T), tab, n, sa, lead, h->sweeps_launch, \
-           b->rest_groups, b->rest_wgs)
+           b->seam_lv0, b->rest_groups, b->rest_wgs)
                     if (lead == 0 && b->seam_levels == 0) LAUNCH_REST(false, true);
                     else if (lead == 0) LAUNCH_REST(true, true);
                     else if (b->seam_levels == 0) LAUNCH_REST(false, false);
@@ -3299,6 +3313,23 @@ RestShape rest_shape(const lbfd_params *p, int narrow, int cus)
     return RestShape{REST_LEAD, std::min(narrow, most), false};
 }
 
+// First seam level that goes to one workgroup: the row and column of 2-D and the edges of 3-D
+// where they have at most SEAM_WALK nodes, else (and for the planes of 3-D) what comes after
+// them. One workgroup takes as many turns as it has nodes per thread, all workgroups a launch or
+// a meeting more per half-sweep (45 to 60 sweeps, FP64, ms a step with one workgroup and
+// with all: 361^2 1.09 and 1.17, 601^2 2.04 and 1.94, 2047^2 7.80 and 5.80, 63 x 4001 3.80 and
+// 1.71, 9 x 9 x 401 1.95 and 1.98, 9 x 9 x 801 2.66 and 2.30, 9 x 9 x 3201 6.94 and 3.73).
+constexpr long long SEAM_WALK = 768;
+int seam_lv0(const lbfd_params *p)
+{
+    const int m = seam_axes(p);
+    const bool three = p->lattice == LBFD_D3Q19;
+    const auto along = [&](int axis, int others) { return (m & others) == others ? axis : 0; };
+    const long long n = three ? (long long)along(p->nx, 6) + along(p->ny, 5) + along(p->nz, 3)
+                              : (long long)along(p->nx, 2) + along(p->ny, 1);
+    return (three ? 2 : 1) + (n > SEAM_WALK ? 1 : 0);
+}
+
 // Launch shape of a handle: rows of 64 x per workgroup of the step's node kernels,
 // the grid of the SOR half-sweep launches (workgroups of 256 per compute unit, capped
 // at one per tile of a colour; a multiple of 8 keeps the XCD-aware tile order) and the
@@ -3319,6 +3350,7 @@ void apply_shape(lbfd_handle *h, int rows, int wg_per_cu, int narrow)
     h->sor_lead = r.lead;
     h->rest_wgs = r.wgs;
     h->rest_near = r.near;
+    h->seam_lv0 = seam_lv0(p);
 }
 
 // The same for a batch, by its largest instance: a group on one XCD per instance. Instances
@@ -3332,6 +3364,8 @@ void batch_rest_shape(lbfd_batch *b)
     b->sor_lead = t <= REST_NEAR ? 0 : REST_LEAD;
     b->rest_wgs = (int)std::min<long long>(t, REST_NEAR);
     b->rest_groups = std::min(b->n, 256);
+    b->seam_lv0 = 1;
+    for (const lbfd_handle *h : b->inst) b->seam_lv0 = std::max(b->seam_lv0, h->seam_lv0);
 }
 
 struct Dispatch {
