@@ -4027,9 +4027,6 @@ int lbfd_sg_get_params(lbfd_sg *s, float *host, int64_t n)
 
 static unsigned blocks_for(long long n, long long per) { return (unsigned)((n + per - 1) / per); }
 
-// Output planes per column of the z-marching forward kernel.
-constexpr int SG_ZC = 32;
-
 extern "C++" {
 // k_conv_rows over an output grid (the source grid is 2 smaller or larger along every axis).
 template <int CIN, int KIND>
@@ -4044,17 +4041,17 @@ static void sg_conv_rows(const lbfd_sg *s, hipStream_t st, const uint16_t *in, c
                        Do + g, Ho + g, Wo + g, Do, Ho, Wo, ry, nyb, (int)units);
 }
 
-// k_conv_fwd_zm over an input grid: columns of 30 x 8 output nodes over SG_ZC planes.
+// k_conv_fwd_zm over an input grid: columns of 30 x 8 output nodes.
 template <int CIN, bool RELU, bool OUTF32>
 static void sg_conv_zm(const lbfd_sg *s, hipStream_t st, const uint16_t *in, const uint16_t *wb, const float *bias,
                        void *out, int B, int Di, int Hi, int Wi)
 {
-    const int nbx = (Wi - 2 + sg::ZX - 1) / sg::ZX, nby = (Hi - 2 + sg::ZY - 1) / sg::ZY,
-              nbz = (Di - 2 + SG_ZC - 1) / SG_ZC;
-    const long long ncol = (long long)nbx * nby * nbz * B;
+    const int nbx = (Wi - 2 + sg::ZX - 1) / sg::ZX, nby = (Hi - 2 + sg::ZY - 1) / sg::ZY;
     const long long most = std::max(8, s->cus * sg::zm_per_cu<CIN>() / 8 * 8);
+    const int zc = sg::planes_per_column((long long)nbx * nby * B, Di - 2, most), nbz = (Di - 2 + zc - 1) / zc;
+    const long long ncol = (long long)nbx * nby * nbz * B;
     hipLaunchKernelGGL((sg::k_conv_fwd_zm<CIN, RELU, OUTF32>), dim3((unsigned)std::min((ncol + 7) / 8 * 8, most)),
-                       dim3(256), 0, st, in, wb, bias, out, Di, Hi, Wi, nbx, nby, nbz, SG_ZC, ncol);
+                       dim3(256), 0, st, in, wb, bias, out, Di, Hi, Wi, nbx, nby, nbz, zc, ncol);
 }
 
 // Weight and bias gradients of layer l from its input x and its output gradient, on B grids of

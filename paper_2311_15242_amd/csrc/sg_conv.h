@@ -346,6 +346,28 @@ __global__ __launch_bounds__(256, (zm_per_cu<CIN>())) void k_conv_fwd_zm(
     }
 }
 
+// Output planes of a column of k_conv_fwd_zm, for `columns` columns over the whole depth Do and a
+// grid of at most `most` workgroups: the fewest rounds, each as long as its planes and
+// the time of some three more that a column takes to start (2 and 5 measure the same). More
+// than ZC gain nothing. Grids of few columns in the plane are cut along z until all
+// workgroups have one: four layers over 72^3 input nodes 323 -> 108 us, 12 x 12 x 68 86 -> 31,
+// 208 x 9 x 208 314 -> 85, 100^3 326 -> 221, 264^3 3320 -> 3220 (always 32 planes before).
+constexpr int ZC = 32, COL_START = 3;
+inline int planes_per_column(long long columns, int Do, long long most)
+{
+    int best = 1;
+    long long least = 0;
+    for (int zc = 1; zc <= ZC && zc <= Do; ++zc) {
+        const long long n = columns * ((Do + zc - 1) / zc), wgs = std::min((n + 7) / 8 * 8, most);
+        const long long cost = ((n + 7) / 8 + wgs / 8 - 1) / (wgs / 8) * (zc + COL_START);
+        if (zc == 1 || cost <= least) {
+            least = cost;
+            best = zc;
+        }
+    }
+    return best;
+}
+
 // The same sums over rows of a narrower grid, output nodes in their order in memory.
 //
 // FWD:   out[m][o] = max(0, b[o] + sum_{tap,i} in[m + tap][i] w[tap][i][o])   BF16 [M][32]
