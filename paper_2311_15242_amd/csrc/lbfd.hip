@@ -4034,11 +4034,13 @@ static void sg_conv_rows(const lbfd_sg *s, hipStream_t st, const uint16_t *in, c
                          const uint16_t *mask, void *out, int B, int Do, int Ho, int Wo)
 {
     const int g = KIND == sg::DGRAD ? -2 : 2;
-    const int ry = sg::rows_per_unit(B, Do, Ho, Wo, s->cus), nyb = (Ho + ry - 1) / ry;
-    const long long units = (long long)B * Do * nyb;
+    const sg::RowsUnit r = sg::rows_unit(B, Do, Ho, Wo, s->cus);
+    const int nyb = (Ho + r.ry - 1) / r.ry, nzb = (Do + r.rz - 1) / r.rz;
+    const long long units = (long long)B * nzb * nyb;
     const long long grid = std::min<long long>((units + 7) / 8 * 8, std::max(8, s->cus / 8 * 8));
-    hipLaunchKernelGGL((sg::k_conv_rows<CIN, KIND>), dim3((unsigned)grid), dim3(256), 0, st, in, wb, bias, mask, out,
-                       Do + g, Ho + g, Wo + g, Do, Ho, Wo, ry, nyb, (int)units);
+    const auto kernel = r.rz > 1 ? sg::k_conv_rows<CIN, KIND, true> : sg::k_conv_rows<CIN, KIND, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), 0, st, in, wb, bias, mask, out, Do + g, Ho + g, Wo + g,
+                       Do, Ho, Wo, r.ry, nyb, r.rz, nzb, (int)units);
 }
 
 // k_conv_fwd_zm over an input grid: columns of 30 x 8 output nodes.

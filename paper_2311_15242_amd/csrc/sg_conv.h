@@ -378,8 +378,8 @@ inline int planes_per_column(long long columns, int Do, long long most)
 // in: channels-last BF16 [B][Ds][Hs][Ws][CIN], wb in fragment order; output grid Do, Ho, Wo (Ds - 2
 // .. for the forward layers, Ds + 2 .. for DGRAD).
 //
-// A unit of work is ry rows of one output plane. Its input (3 planes of ry + 2 rows of Wo + 2
-// nodes) is staged in LDS while the unit before is computed (two buffers, registers in
+// A unit of work is ry rows of one output plane, or rz whole planes. Its input (rz + 2 planes of
+// ry + 2 rows of Wo + 2 nodes) is staged in LDS while the unit before is computed (two buffers, registers in
 // between); consecutive output nodes, whatever rows they lie in, form the 32-row tiles of the
 // matrix instructions, so narrow rows waste nothing. The weights stay in registers, a wavefront
 // per SIMD; each wavefront takes tiles in pairs that share a weight fragment. Units are
@@ -391,19 +391,21 @@ inline int planes_per_column(long long columns, int Do, long long most)
 // gradient 119 -> 49 (66 with its mask read where it is applied); a 24^3 grid 30 -> 9 us a layer.
 enum { FWD = 0, LAST = 1, DGRAD = 2 };
 constexpr int ROWS_NODES = 1000;   // staged nodes of a unit at most (two buffers fill the LDS)
-template <int CIN, int KIND>
+// PLANES: rz may be more than one (its divisions cost units of rows 2 to 4 %).
+template <int CIN, int KIND, bool PLANES>
 __global__ __launch_bounds__(256, 1) void k_conv_rows(const u16 *__restrict__ in, const u16 *__restrict__ wb,
                                                      const float *__restrict__ bias, const u16 *__restrict__ mask,
                                                      void *__restrict__ out, int Ds, int Hs, int Ws, int Do, int Ho,
-                                                     int Wo, int ry, int nyb, int units)
+                                                     int Wo, int ry, int nyb, int planes, int nzb, int units)
 {
+    const int rz = PLANES ? planes : 1;
     constexpr int CP = CIN + 8, NC = CIN / 16, PCS = CIN / 8;
     constexpr int PPT = (ROWS_NODES * PCS + 255) / 256;
     constexpr int OFF = KIND == DGRAD ? 2 : 0;
     __shared__ __attribute__((aligned(16))) u16 buf[2][ROWS_NODES * CP];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int mr = lane & 31, kg = lane >> 5;
-    const int SW = Wo + 2, SR = ry + 2, nodes = 3 * SR * SW;
+    const int SW = Wo + 2, SR = ry + 2, nodes = (rz + 2) * SR * SW;
     bf16x8 Bw[27][NC];
 #pragma unroll
     for (int t = 0; t < 27; ++t)
@@ -424,8 +426,8 @@ __global__ __launch_bounds__(256, 1) void k_conv_rows(const u16 *__restrict__ in
         Unit w;
         const int t = u / nyb;
         w.y0 = (u - t * nyb) * ry;
-        w.b = t / Do;
-        w.z = t - w.b * Do;
+        w.b = t / (PLANES ? nzb : Do);
+        w.z = (t - w.b * (PLANES ? nzb : Do)) * rz;
         return w;
     };
     u32x4 v[PPT];
@@ -454,7 +456,8 @@ __global__ __launch_bounds__(256, 1) void k_conv_rows(const u16 *__restrict__ in
 #pragma unroll
         for (int i = 0; i < NT; ++i) {
             const int j = min(32 * (t + i) + mr, n - 1), yy = j / Wo;
-            base[i] = s + (yy * SW + (j - yy * Wo)) * CP + kg * 8;
+            const int row = PLANES ? yy + 2 * (yy / Ho) : yy;   // two rows between the planes of a unit
+            base[i] = s + (row * SW + (j - yy * Wo)) * CP + kg * 8;
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][e] = 0.0f;
             if constexpr (KIND == DGRAD)
@@ -525,7 +528,7 @@ __global__ __launch_bounds__(256, 1) void k_conv_rows(const u16 *__restrict__ in
         const bool more = u + step < uend;
         if (more) fetch(u + step);
         const Unit w = unit_of(u);
-        const int n = min(ry, Ho - w.y0) * Wo, nt = (n + 31) / 32, per = (nt + 3) / 4;
+        const int n = (PLANES ? min(rz, Do - w.z) : 1) * min(ry, Ho - w.y0) * Wo, nt = (n + 31) / 32, per = (nt + 3) / 4;
         const long long m0 = ((long long)(w.b * Do + w.z) * Ho + w.y0) * Wo;
         const int tend = min(nt, (wave + 1) * per);
         int t = wave * per;
@@ -536,22 +539,27 @@ __global__ __launch_bounds__(256, 1) void k_conv_rows(const u16 *__restrict__ in
     }
 }
 
-// Rows of a unit of k_conv_rows for an output grid: the fewest rounds over `cus` workgroups, each as
-// long as the wavefront with the most tiles (54 matrix instructions of 32 cycles a tile with 32
-// input channels, and some 1500 cycles a unit for its start, end and barrier).
-inline int rows_per_unit(int B, int Do, int Ho, int Wo, int cus)
+// Unit of k_conv_rows for an output grid: the fewest rounds over `cus` workgroups, each as long
+// as the wavefront with the most tiles (54 matrix instructions of 32 cycles a tile with 32 input
+// channels, and some 1500 cycles a unit for its start, end and barrier). Several planes where one
+// has few tiles: 512 grids of 12^3 input nodes, four layers, 188 us with one plane a unit.
+struct RowsUnit {
+    int ry, rz;
+};
+inline RowsUnit rows_unit(int B, int Do, int Ho, int Wo, int cus)
 {
-    int best = 1;
-    double least = 0.0;
-    for (int ry = 1; ry <= Ho && 3 * (ry + 2) * (Wo + 2) <= ROWS_NODES; ++ry) {
-        const long long units = (long long)B * Do * ((Ho + ry - 1) / ry);
-        const int tiles = (ry * Wo + 31) / 32;
+    RowsUnit best{1, 1};
+    double least = -1.0;
+    const auto consider = [&](int ry, int rz) {
+        const long long units = (long long)B * ((Do + rz - 1) / rz) * ((Ho + ry - 1) / ry);
+        const int tiles = (rz * ry * Wo + 31) / 32;
         const double cost = (double)((units + cus - 1) / cus) * (54.0 * 32.0 * ((tiles + 3) / 4) + 1500.0);
-        if (ry == 1 || cost < least) {
-            least = cost;
-            best = ry;
-        }
-    }
+        if (least >= 0.0 && cost >= least) return;
+        least = cost;
+        best = RowsUnit{ry, rz};
+    };
+    for (int ry = 1; ry <= Ho && 3 * (ry + 2) * (Wo + 2) <= ROWS_NODES; ++ry) consider(ry, 1);
+    for (int rz = 2; rz <= Do && (rz + 2) * (Ho + 2) * (Wo + 2) <= ROWS_NODES; ++rz) consider(Ho, rz);
     return best;
 }
 
