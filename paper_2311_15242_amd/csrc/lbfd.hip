@@ -3515,8 +3515,11 @@ int lbfd_create(const lbfd_params *p, void *d_workspace, size_t bytes, void *str
     fill_kp(h->kd, p, h->ws, Lo);
     fill_kp(h->kf, p, h->ws, Lo);
     h->obs_out = (double *)(h->ws + Lo.obs);
-    hipLaunchKernelGGL(k_sync_clear, dim3(1), dim3(256), 0, h->stream, h->kd.fld.sync);
-    if (hipGetLastError() != hipSuccess) {
+    // this launch's own status: an error that another call of the thread left pending is not ours
+    SorSync *sync = h->kd.fld.sync;
+    void *args[] = {&sync};
+    if (hipLaunchKernel((const void *)k_sync_clear, dim3(1), dim3(256), args, 0, h->stream) != hipSuccess) {
+        (void)hipGetLastError();
         delete h;
         return LBFD_EHIP;
     }
