@@ -83,7 +83,7 @@ class Tuning(C.Structure):
 
 
 # Launch shape of the library's defaults (64 x 4 node tiles, 8 SOR workgroups per
-# compute unit, 256 for sweeps past the third) and the table of tuned shapes the
+# compute unit, at most 256 for the persistent solve) and the table of tuned shapes the
 # autotuner writes (tuning.json next to this module), keyed by tuning_key.
 DEFAULT_TUNING = dict(rows=4, sor_wg_per_cu=8, sor_narrow=256)
 TUNING_FILE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tuning.json")
