@@ -1785,15 +1785,15 @@ __global__ __launch_bounds__(REST_T, 2) void k_sor_rest(KP<typename P::R> k, int
     sor_sweeps<LAT, P, SEAM, ROWS>(k, step_args(k), g, first, nsw, lv0, open, sh);
 }
 
-// Batch: `groups` groups of `per` workgroups (group i on the XCD i mod 8), group i solving the
-// instances i, i + groups, ... one after another: the pair arrays of an instance stay in
-// that XCD's L2 from phase to phase, and while one group meets another one works.
+// Batch: `groups` groups of `per` workgroups, group i on the `span` XCDs from span i mod 8 on,
+// solving the instances i, i + groups, ... one after another: the pair arrays of an instance stay
+// in the L2 of those XCDs from phase to phase, and while one group meets another one works.
 template <int LAT, class P, bool SEAM, bool ROWS>
 __global__ __launch_bounds__(REST_T, ROWS ? 2 : 4) void kb_sor_rest(const KP<typename P::R> *tab, int ninst, StepArgs sa, int first,
-                                                     int nsw, int lv0, int groups, int per)
+                                                     int nsw, int lv0, int groups, int per, int span)
 {
     __shared__ SorShared sh;
-    const int i0 = (int)(blockIdx.x >> 3) / per * 8 + (int)(blockIdx.x & 7u);
+    const int i0 = (int)(blockIdx.x >> 3) / (per / span) * (8 / span) + (int)(blockIdx.x & 7u) / span;
     if (i0 >= groups) return;
     SorGroup g{nullptr, 0u, 0u, 0u};
     for (int i = i0; i < ninst; i += groups) {
@@ -2410,7 +2410,8 @@ struct lbfd_batch {
     int seam_lv0;       // as for a single handle, the same for every instance
     int sor_lead;       // as for a single handle, the same for every instance
     int rest_groups;    // groups of the persistent solve (each takes every rest_groups-th instance)
-    int rest_wgs;       // workgroups of a group
+    int rest_span;      // XCDs that a group has workgroups on (1, 2, 4 or 8)
+    int rest_wgs;       // workgroups of a group, a multiple of rest_span
     int rows = BY;      // rows of 64 x per workgroup of the node kernels (every instance)
     StepGraphs graphs;
 };
@@ -3023,10 +3024,11 @@ template <int LAT, class P> struct Impl {
                                -b->seam_lv0, 0, s);
                 }
                 if (lead < h->sweeps_launch) {
-                    const dim3 gr((unsigned)(8 * ((b->rest_groups + 7) / 8) * b->rest_wgs));
+                    const int beside = 8 / b->rest_span;   // groups on the eight XCDs
+                    const dim3 gr((unsigned)((b->rest_groups + beside - 1) / beside * beside * b->rest_wgs));
 #define LAUNCH_REST(SEAM, ROWS)                                                                          \
     LAUNCH(KC_SOR, (kb_sor_rest<LAT, P, SEAM, ROWS>), gr, dim3(REST_T), tab, n, sa, lead, h->sweeps_launch, \
-           b->seam_lv0, b->rest_groups, b->rest_wgs)
+           b->seam_lv0, b->rest_groups, b->rest_wgs, b->rest_span)
                     if (lead == 0 && b->seam_levels == 0) LAUNCH_REST(false, true);
                     else if (lead == 0) LAUNCH_REST(true, true);
                     else if (b->seam_levels == 0) LAUNCH_REST(false, false);
@@ -3357,13 +3359,24 @@ void apply_shape(lbfd_handle *h, int rows, int wg_per_cu, int narrow)
 // of up to one tile per workgroup are solved by it from the first sweep on (8 instances of
 // up to 64 x 192 nodes: 18 us against 37 us of launches); larger ones by launches over all
 // instances first (64 columns of 1e5 nodes: 0.37 ms against 0.44).
+//
+// With fewer instances than XCDs a group has workgroups on several, so that none is left idle
+// (FP64, 60 sweeps, ms a step with groups on one, two, four and eight XCDs: one instance
+// of 1024^2 6.06, 3.50, 2.19, 1.71; two 6.32, 3.84, 2.59, 2.64; four 6.97, 4.56, 4.24, 11.1).
+// Where their number does not divide the XCDs, groups share some if a member has eight tiles or
+// more with them (five instances of 1601^2 26.2 on one XCD each, 20.7 on two); with
+// fewer a phase is latency, and the nearer group is the faster (five of 300 x 256 0.92 and 1.13).
 void batch_rest_shape(lbfd_batch *b)
 {
     long long t = 1;
     for (const lbfd_handle *h : b->inst) t = std::max(t, rest_tiles(&h->p));
     b->sor_lead = t <= REST_NEAR ? 0 : REST_LEAD;
-    b->rest_wgs = (int)std::min<long long>(t, REST_NEAR);
     b->rest_groups = std::min(b->n, 256);
+    int span = 1;
+    if (t > REST_NEAR)
+        while (2 * span * b->rest_groups <= 8 || (span * b->rest_groups < 8 && t >= 8 * REST_NEAR * span)) span *= 2;
+    b->rest_span = span;
+    b->rest_wgs = (int)std::min<long long>((t + span - 1) / span, REST_NEAR) * span;
     b->seam_lv0 = 1;
     for (const lbfd_handle *h : b->inst) b->seam_lv0 = std::max(b->seam_lv0, h->seam_lv0);
 }
