@@ -266,6 +266,14 @@ typedef struct {
 int lbfd_set_tuning(lbfd_handle *h, const lbfd_tuning *t);
 int lbfd_get_tuning(const lbfd_handle *h, lbfd_tuning *t);
 
+/* Most workgroups (0: as many as the grid gives work) of the launch that iterates
+ * the implicit solve, and how many of them its group waits for some
+ * microseconds (at most 65536; 0 or fewer than there are: all of them) before it
+ * goes on with those that are running. A busy device makes a group smaller by
+ * itself; this does it on purpose, and never changes the results. Synchronises the
+ * stream and drops captured graphs. Errors: EINVAL, EHIP. */
+int lbfd_set_solve_group(lbfd_handle *h, int32_t most, int32_t expected);
+
 /* Release the handle (not the caller's workspace or stream). */
 void lbfd_destroy(lbfd_handle *h);
 
@@ -307,6 +315,9 @@ int lbfd_batch_step(lbfd_batch *b, int64_t n);
  * `sor_narrow` do not change them).
  * Errors: EINVAL, EHIP. */
 int lbfd_batch_set_tuning(lbfd_batch *b, const lbfd_tuning *t);
+
+/* The same as lbfd_set_solve_group for the group of each instance of a batch. */
+int lbfd_batch_set_solve_group(lbfd_batch *b, int32_t most, int32_t expected);
 
 /* Graph replay of lbfd_batch_step, as lbfd_set_graphs for one handle. */
 int lbfd_batch_set_graphs(lbfd_batch *b, int32_t enable);

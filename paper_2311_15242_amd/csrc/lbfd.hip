@@ -1771,16 +1771,17 @@ __device__ __forceinline__ void sor_sweeps(const KP<typename P::R> &k, const Ste
 }
 
 // near: only the workgroups of one residue mod 8 take part. The hardware deals workgroups to
-// the eight XCDs in turn, so these share an L2.
+// the eight XCDs in turn, so these share an L2. want: those that take part, or more (the group
+// is then closed early).
 template <int LAT, class P, bool SEAM, bool ROWS>
 __global__ __launch_bounds__(REST_T, 2) void k_sor_rest(KP<typename P::R> k, int first, int nsw, int lv0,
-                                                         int near)
+                                                         int near, int want)
 {
     __shared__ SorShared sh;
     if (near && (blockIdx.x & 7u) != 0u) return;
     const uint32_t open = sor_open<LAT, P>(k, first, sh);
     if (open == 0u) return;   // the usual case after some sweeps by launches
-    SorGroup g = sor_enrol(k.fld.sync, near ? gridDim.x >> 3 : gridDim.x, sh);
+    SorGroup g = sor_enrol(k.fld.sync, (uint32_t)want, sh);
     if (g.members == 0u) return;
     sor_sweeps<LAT, P, SEAM, ROWS>(k, step_args(k), g, first, nsw, lv0, open, sh);
 }
@@ -1790,7 +1791,7 @@ __global__ __launch_bounds__(REST_T, 2) void k_sor_rest(KP<typename P::R> k, int
 // in the L2 of those XCDs from phase to phase, and while one group meets another one works.
 template <int LAT, class P, bool SEAM, bool ROWS>
 __global__ __launch_bounds__(REST_T, ROWS ? 2 : 4) void kb_sor_rest(const KP<typename P::R> *tab, int ninst, StepArgs sa, int first,
-                                                     int nsw, int lv0, int groups, int per, int span)
+                                                     int nsw, int lv0, int groups, int per, int span, int want)
 {
     __shared__ SorShared sh;
     const int i0 = (int)(blockIdx.x >> 3) / (per / span) * (8 / span) + (int)(blockIdx.x & 7u) / span;
@@ -1800,7 +1801,7 @@ __global__ __launch_bounds__(REST_T, ROWS ? 2 : 4) void kb_sor_rest(const KP<typ
         const uint32_t open = sor_open<LAT, P>(tab[i], first, sh);
         if (open == 0u) continue;
         if (!g.s) {
-            g = sor_enrol(tab[i0].fld.sync, (uint32_t)per, sh);
+            g = sor_enrol(tab[i0].fld.sync, (uint32_t)want, sh);
             if (g.members == 0u) return;
         }
         sor_sweeps<LAT, P, SEAM, ROWS>(tab[i], sa, g, first, nsw, lv0, open, sh);
@@ -2374,6 +2375,8 @@ struct lbfd_handle {
     int sor_lead;       // sweeps done by half-sweep launches; the persistent solve takes the others
     int rest_wgs;       // workgroups of the persistent solve
     bool rest_near;     // they all sit on one XCD
+    int rest_want = 0;  // workgroups its group waits for, where they are not all of them (0)
+    int rest_cap = 0;   // most workgroups of the persistent solve by the caller's wish (0: none)
     int seam_tiles;     // workgroups over the seam index space (0: no seam classes)
     int seam_levels;    // seam levels (periodic axes of odd extent)
     int seam_lv0;       // the first one that goes to one workgroup
@@ -2412,6 +2415,7 @@ struct lbfd_batch {
     int rest_groups;    // groups of the persistent solve (each takes every rest_groups-th instance)
     int rest_span;      // XCDs that a group has workgroups on (1, 2, 4 or 8)
     int rest_wgs;       // workgroups of a group, a multiple of rest_span
+    int rest_want = 0, rest_cap = 0;   // as for a single handle, of a group
     int rows = BY;      // rows of 64 x per workgroup of the node kernels (every instance)
     StepGraphs graphs;
 };
@@ -2869,7 +2873,8 @@ template <int LAT, class P> struct Impl {
             const dim3 gr(h->rest_near ? 8 * h->rest_wgs : h->rest_wgs);
             const int near = (int)h->rest_near;
 #define LAUNCH_REST(SEAM, ROWS) \
-    LAUNCH(KC_SOR, (k_sor_rest<LAT, P, SEAM, ROWS>), gr, dim3(REST_T), k, lead, h->sweeps_launch, h->seam_lv0, near)
+    LAUNCH(KC_SOR, (k_sor_rest<LAT, P, SEAM, ROWS>), gr, dim3(REST_T), k, lead, h->sweeps_launch, h->seam_lv0, near, \
+           std::max(h->rest_wgs, h->rest_want))
             if (lead == 0 && h->seam_levels == 0) LAUNCH_REST(false, true);
             else if (lead == 0) LAUNCH_REST(true, true);
             else if (h->seam_levels == 0) LAUNCH_REST(false, false);
@@ -3028,7 +3033,7 @@ template <int LAT, class P> struct Impl {
                     const dim3 gr((unsigned)((b->rest_groups + beside - 1) / beside * beside * b->rest_wgs));
 #define LAUNCH_REST(SEAM, ROWS)                                                                          \
     LAUNCH(KC_SOR, (kb_sor_rest<LAT, P, SEAM, ROWS>), gr, dim3(REST_T), tab, n, sa, lead, h->sweeps_launch, \
-           b->seam_lv0, b->rest_groups, b->rest_wgs, b->rest_span)
+           b->seam_lv0, b->rest_groups, b->rest_wgs, b->rest_span, std::max(b->rest_wgs, b->rest_want))
                     if (lead == 0 && b->seam_levels == 0) LAUNCH_REST(false, true);
                     else if (lead == 0) LAUNCH_REST(true, true);
                     else if (b->seam_levels == 0) LAUNCH_REST(false, false);
@@ -3350,7 +3355,7 @@ void apply_shape(lbfd_handle *h, int rows, int wg_per_cu, int narrow)
     h->sor_narrow = narrow;
     const RestShape r = rest_shape(p, narrow, h->cus);
     h->sor_lead = r.lead;
-    h->rest_wgs = r.wgs;
+    h->rest_wgs = h->rest_cap ? std::min(h->rest_cap, r.wgs) : r.wgs;
     h->rest_near = r.near;
     h->seam_lv0 = seam_lv0(p);
 }
@@ -3377,6 +3382,10 @@ void batch_rest_shape(lbfd_batch *b)
         while (2 * span * b->rest_groups <= 8 || (span * b->rest_groups < 8 && t >= 8 * REST_NEAR * span)) span *= 2;
     b->rest_span = span;
     b->rest_wgs = (int)std::min<long long>((t + span - 1) / span, REST_NEAR) * span;
+    if (b->rest_cap && b->rest_cap < b->rest_wgs) {
+        b->rest_span = 1;
+        b->rest_wgs = std::min(b->rest_cap, REST_NEAR);
+    }
     b->seam_lv0 = 1;
     for (const lbfd_handle *h : b->inst) b->seam_lv0 = std::max(b->seam_lv0, h->seam_lv0);
 }
@@ -3651,6 +3660,28 @@ int lbfd_batch_set_tuning(lbfd_batch *b, const lbfd_tuning *t)
         return LBFD_EHIP;
     b->grid_node = dim3((unsigned)pn[b->n]);
     b->rows = t->rows;
+    return LBFD_OK;
+}
+
+int lbfd_set_solve_group(lbfd_handle *h, int32_t most, int32_t expected)
+{
+    if (!h || most < 0 || expected < 0 || expected > 65536) return LBFD_EINVAL;
+    if (hipStreamSynchronize(h->stream) != hipSuccess) return LBFD_EHIP;
+    h->graphs.drop();
+    h->rest_cap = most;
+    h->rest_want = expected;
+    apply_shape(h, h->rows, h->sor_wg_per_cu, h->sor_narrow);
+    return LBFD_OK;
+}
+
+int lbfd_batch_set_solve_group(lbfd_batch *b, int32_t most, int32_t expected)
+{
+    if (!b || most < 0 || expected < 0 || expected > 65536) return LBFD_EINVAL;
+    if (hipStreamSynchronize(b->stream) != hipSuccess) return LBFD_EHIP;
+    b->graphs.drop();
+    b->rest_cap = most;
+    b->rest_want = expected;
+    batch_rest_shape(b);
     return LBFD_OK;
 }
 

@@ -26,6 +26,7 @@ EXPORTED = ["lbfd_workspace_bytes", "lbfd_create", "lbfd_init_fields", "lbfd_set
             "lbfd_batch_step", "lbfd_batch_destroy", "lbfd_set_graphs", "lbfd_batch_set_graphs",
             "lbfd_fd_substeps", "lbfd_set_fd", "lbfd_write_field", "lbfd_read_field_noalloc",
             "lbfd_set_tuning", "lbfd_get_tuning", "lbfd_batch_set_tuning",
+            "lbfd_set_solve_group", "lbfd_batch_set_solve_group",
             "lbfd_sg_n_params", "lbfd_sg_workspace_bytes", "lbfd_sg_create", "lbfd_sg_set_params",
             "lbfd_sg_get_params", "lbfd_sg_forward", "lbfd_sg_gradient", "lbfd_sg_train_step", "lbfd_sg_features",
             "lbfd_sg_snapshot", "lbfd_sg_tiles", "lbfd_sg_advance", "lbfd_sg_destroy", "lbfd_sg_set_drift_tol",
@@ -157,6 +158,8 @@ def load(build_if_missing: bool = False):
     L.lbfd_set_tuning.argtypes = [vp, P(Tuning)]
     L.lbfd_get_tuning.argtypes = [vp, P(Tuning)]
     L.lbfd_batch_set_tuning.argtypes = [vp, P(Tuning)]
+    L.lbfd_set_solve_group.argtypes = [vp, C.c_int32, C.c_int32]
+    L.lbfd_batch_set_solve_group.argtypes = [vp, C.c_int32, C.c_int32]
     L.lbfd_profile.argtypes = [vp, C.c_int32]
     L.lbfd_profile_read.argtypes = [vp, C.c_int32, P(C.c_char_p), dp, P(C.c_int64), P(C.c_int32)]
     L.lbfd_destroy.argtypes = [vp]
