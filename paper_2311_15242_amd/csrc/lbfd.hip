@@ -2062,16 +2062,6 @@ template <int NV> __device__ __forceinline__ void block_sum_store(double (&v)[NV
         for (int i = 0; i < NV; ++i) out[i] = sh[i][0];
 }
 
-// Total of G psi + X phi (the conserved integrand of eqs 20-21), FP64, at `level`, psi/phi from
-// buffer `buf` times `mult` (mult < 0: the device's rescaling factor, which turns stored
-// values into physical ones), and what follows from it (mode). One launch: every workgroup
-// leaves its sum, and the one that finds all the others' there adds them up, always in the
-// same order. After a solve (nsw > 0) workgroup 0 also records its sweeps and clears what it
-// left, beside the others' sums.
-//
-// Bound: HBM on large grids (4.5 TB/s at 6.3e6 nodes), latency on small ones, hence up to
-// TOTAL_BLOCKS workgroups and no second launch for the final sum (128^2 nodes: 17 us in two
-// launches, of 4096 nodes a workgroup).
 // Sum over the workgroup in thread 0, always in the same order. sh: one value per wavefront.
 __device__ __forceinline__ double block_sum(double v, double *sh)
 {
@@ -2086,6 +2076,17 @@ __device__ __forceinline__ double block_sum(double v, double *sh)
         for (int w = 0; w < nw; ++w) v += sh[w];
     return v;
 }
+
+// Total of G psi + X phi (the conserved integrand of eqs 20-21), FP64, at `level`, psi/phi from
+// buffer `buf` times `mult` (mult < 0: the device's rescaling factor, which turns stored
+// values into physical ones), and what follows from it (mode). One launch: every workgroup
+// leaves its sum, and the one that finds all the others' there adds them up, always in the
+// same order. After a solve (nsw > 0) workgroup 0 also records its sweeps and clears what it
+// left, beside the others' sums.
+//
+// Bound: HBM on large grids (4.5 TB/s at 6.3e6 nodes), latency on small ones, hence up to
+// TOTAL_BLOCKS workgroups and no second launch for the final sum (128^2 nodes: 17 us in two
+// launches, of 4096 nodes a workgroup).
 template <int LAT, class P>
 __device__ __forceinline__ void total_body(const KP<typename P::R> &k, int level, int buf, double mult, int blk,
                                            int nblk, int from_split, int mode, int nsw)
